@@ -82,7 +82,7 @@ def draw(rng):
     if op == "truncate":
         n = rng.randint(8, 16)
         return {"op": op, "n": n, "na": n // 2, "nb": n // 2 - rng.choice([0, 1]), "nq": rng.randint(2 * n, 6 * n),
-                "M": _log(rng, 24, 512), "k": n // 2 - rng.choice([1, 2])}
+                "M": _log(rng, 24, min(512, 4 ** (n // 2) // 3)), "k": n // 2 - rng.choice([1, 2])}
     if op == "sweep":
         n = rng.randint(5, 8)
         return {"op": op, "n": n, "na": (n + 1) // 2, "nb": n // 2, "nq": rng.randint(8, 4 * n),
@@ -191,7 +191,7 @@ def _inputs(case, seed):
     elif op != "sweep":
         x["bonds"], x["sites"] = _mps(case, rng)
         if op != "grad":
-            x["psi"] = _two_site(x["bonds"], case["k"], rng, 3.0 if op == "truncate" else None)
+            x["psi"] = _two_site(x["bonds"], case["k"], rng, 10.0 if op == "truncate" else None)
     return x
 
 
