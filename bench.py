@@ -27,9 +27,9 @@ N_ORB, N_CHOL, M, SEED = 20, 120, 1024, 0
 MID = N_ORB // 2 - 1
 PEAK_FP64 = 78.6  # TFLOP/s, MI355X dense FP64 matrix
 # HBM bytes per launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
-# runs (profiles/sigma_step_kernels_cas20_m1024_fp64_counters.md), scaled by the same counters on a
-# plain copy (fetch x2.0, write x1.0); set to None whenever that kernel changes.
-TRAFFIC = 2.49e10
+# runs, scaled by the same counters on a plain copy (fetch x2.0, write x1.0); None where the
+# kernel has changed since they were taken.
+TRAFFIC = None
 
 
 def _host_info():
@@ -638,7 +638,7 @@ def main():
         "setup_s": t_setup,
         "energy_last": energies[-1] if energies else None,
         "plan_reuse_per_step": (d["plan_hits"]) / args.steps,
-        "roofline": {"bound": "mfma", "kernel": "gemm_wg<double, 4> (sigma phase B, timed launches)",
+        "roofline": {"bound": "mfma", "kernel": "gemm_stream<double, 4> (sigma phase B, timed launches)",
                      "achieved": b_achieved, "peak": PEAK_FP64, "unit": "TFLOP/s",
                      "frac": b_achieved / PEAK_FP64, "traffic": TRAFFIC,
                      "launch_ms": b_launch_ms, "flops_per_launch": b_flops,

@@ -66,6 +66,12 @@ struct SplitTile {
   int acc, pad;
 };
 void launch_splitk_reduce(const SplitTile* tiles, int n, const double* slots, hipStream_t s);
+// NT stream kernel (gemm_stream.hip; prec PREC_F64 or PREC_F32: operands,
+// accumulation and outputs in that type): one wave per unit, tile (16 RB) x
+// (16 CB) with RB = shape >> 3 and CB = shape & 7 in 1..4.  The operands lie in
+// buffers with 64 readable bytes past their end (DevMem's slack); partial tiles
+// (accumulate == 2) are 16 CB wide.
+void launch_gemm_stream(int prec, int tag, const GemmUnit* units, int n_units, const GemmItem* items, hipStream_t s);
 // NT block kernel (prec PREC_F64 or PREC_F32: operands, accumulation and
 // outputs in that type): one 256-thread workgroup per unit, tile (16 RB) x
 // (16 CB) with RB = shape >> 3 in 1..6 and CB = shape & 7 in 1..4; every item

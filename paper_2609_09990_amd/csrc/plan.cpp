@@ -290,6 +290,30 @@ static void add_units(std::vector<PUnit>& units, int cbuf, long coff, int ldc, i
   units.push_back({cbuf, coff, ldc, M, N, 0, 0, ib, ie, acc});
 }
 
+// Cost of one 4-deep k step of an output block, and of its largest tile: in 32 x
+// 32 tiles for the one-wave kernels, in 16 x 16 MFMA blocks plus one per tile
+// (the step's loads and bookkeeping) for the stream kernel.
+static long block_step_cost(const PUnit& u, bool stream) {
+  if (!stream) return (long)((u.M + 31) / 32) * ((u.N + 31) / 32);
+  const int rb = (u.M + 15) / 16, cb = (u.N + 15) / 16;
+  return (long)rb * cb + (long)((rb + 3) / 4) * ((cb + 3) / 4);
+}
+static long tile_step_cost(const PUnit& u, bool stream) {
+  if (!stream) return 1;
+  const int rb = (u.M + 15) / 16, cb = (u.N + 15) / 16;
+  const int nr = (rb + 3) / 4, nc = (cb + 3) / 4;
+  return (long)((rb + nr - 1) / nr) * ((cb + nc - 1) / nc) + 1;
+}
+static double phase_work(const Phase& ph, bool stream) {
+  double w = 0;
+  for (const PUnit& u : ph.units) {
+    long k = 0;
+    for (int i = u.ib; i < u.ie; ++i) k += (ph.items[i].K + 3) / 4;
+    w += (double)k * block_step_cost(u, stream);
+  }
+  return w;
+}
+
 // Host check that every tile of every item stays inside its buffer (in
 // elements); a plan bug becomes an error instead of a device fault.
 // Also returns whether every item fits the buffer-load kernels (buffer_reach_ok).
@@ -361,11 +385,13 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
     }
   }, 4096);
   ph.buf_ok[slot] = buf_ok;
-  // fp64 / fp32 NT phases with long item lists (sigma phase B) take the
-  // workgroup block kernel: whole-block tiles up to 96 x 64, operands read once
-  // per block
-  const bool use_wg = ph.wg && (prec == PREC_F64 || prec == PREC_F32) && ph.mode == GEMM_NT && buf_ok;
-  ph.wg_used[slot] = use_wg;
+  // fp64 / fp32 NT phases with long item lists (sigma phase B) take the stream
+  // kernel: whole blocks up to 64 x 64 per wave, operands read once per block
+  // (phase B at CAS(20,20), M = 1024: 7.5 ms with 64-row workgroup tiles, one
+  // item at a time; 4.9 ms here); bf16 and offsets past the reach take the
+  // one-wave kernels
+  const bool stream = ph.stream && (prec == PREC_F64 || prec == PREC_F32) && ph.mode == GEMM_NT && buf_ok;
+  ph.stream_used[slot] = stream;
   GemmUnit* units = nullptr;
   SplitTile* tiles = nullptr;
   long nun = 0, ntl = 0;
@@ -385,26 +411,37 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
       }
       if (x < n) v.push_back({x, (n - x + 15) / 16 * 16});
     };
+    // stream tiles: as few strips of at most 64 as there can be, of near-equal
+    // numbers of 16-wide MFMA blocks (82 rows: 48 + 48, not 64 + 32)
+    auto even_strips = [](int n, std::vector<std::pair<int, int>>& v) {
+      v.clear();
+      const int nb = (n + 15) / 16, ns = (nb + 3) / 4;
+      for (int i = 0; i < ns; ++i) v.push_back({16 * (nb * i / ns), 16 * (nb * (i + 1) / ns - nb * i / ns)});
+    };
     struct TileShape { int m0, n0, tm, tn, shape; };
-    // one-wave tiles: up to 64 x 32; workgroup block tiles: up to 96 x 64
-    const int wm = use_wg ? 96 : 64, wn = use_wg ? 64 : 32;
     auto tiles_of = [&](const PUnit& u, std::vector<TileShape>& ts) {
       std::vector<std::pair<int, int>> rs, cs;
-      strips(u.M, wm, rs);
-      strips(u.N, wn, cs);
+      if (stream) {
+        even_strips(u.M, rs);
+        even_strips(u.N, cs);
+      } else {
+        strips(u.M, 64, rs);
+        strips(u.N, 32, cs);
+      }
       ts.clear();
       for (auto& r : rs)
         for (auto& c : cs) ts.push_back({r.first, c.first, r.second, c.second, 8 * (r.second / 16) + c.second / 16});
     };
-    // work in MFMA k-steps of 32 x 32 tiles (integers: the same sum in any order)
+    const bool wide = stream && prec == PREC_F64;  // costs in MFMA blocks
+    // work of every block (integers: the same sum in any order)
     const long nu = (long)ph.units.size();
     std::vector<long> wunit(nu, 0);
     parallel_ranges(nu, [&](int, long u0, long u1) {
       for (long x = u0; x < u1; ++x) {
         const PUnit& u = ph.units[x];
         long w = 0;
-        for (int i = u.ib; i < u.ie; ++i) w += (long)((u.M + 31) / 32) * ((u.N + 31) / 32) * ((ph.items[i].K + 3) / 4);
-        wunit[x] = w;
+        for (int i = u.ib; i < u.ie; ++i) w += (ph.items[i].K + 3) / 4;
+        wunit[x] = w * block_step_cost(u, wide);
       }
     }, unit_grain(ph));
     double work = 0;
@@ -413,11 +450,14 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
       for (long w : wunit) wsum += w;
       work = (double)wsum;
     }
-    if (ph.split_work > 0) work = ph.split_work;
-    // about 16384 one-wave units; workgroup units are cut finer (65536, measured
-    // best for sigma phase B at CAS(20,20), M = 1024: smaller pieces of the
-    // largest blocks spread over more CUs, against more split-K partial tiles)
-    const double chunk = std::max(DMRG_SPLIT_MIN, work / (use_wg ? 65536.0 : 16384.0));
+    if (ph.split_work[wide] > 0) work = ph.split_work[wide];
+    // One-wave kernels: about 16384 units.  Stream kernel, fp64: as many, but
+    // at least 128 block steps each (a unit's start costs about as much as 100:
+    // with one unit per block the longest chain of CAS(8,8), M = 60 took 150 us,
+    // cut this way 10 us), and at most 5000 (CAS(20,20), M = 1024: 8.34 ms per
+    // product with 16384 units of 9800, 8.12 with 32768, 8.76 with 65536).  fp32
+    // keeps its pieces (and with them its rounding) at 1/65536 of the work.
+    const double chunk = stream && !wide ? std::max(DMRG_SPLIT_MIN, work / 65536.0) : wide ? std::min(std::max(128.0, work / 16384.0), 5000.0) : std::max(DMRG_SPLIT_MIN, work / 16384.0);
     // pass 1 (parallel over blocks): tiles and item chunks of each block, counts
     struct UnitPlan {
       std::vector<TileShape> ts;
@@ -431,9 +471,10 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
         const PUnit& u = ph.units[x];
         UnitPlan& q = up[x];
         tiles_of(u, q.ts);
+        const double kchunk = chunk / (double)tile_step_cost(u, wide);  // 4-deep k steps per unit
         long w = 0;
         for (int i = u.ib; i < u.ie; ++i) w += (ph.items[i].K + 3) / 4;
-        if ((double)w <= chunk || u.ie - u.ib <= 1) {
+        if ((double)w <= kchunk || u.ie - u.ib <= 1) {
           q.n_units = (long)q.ts.size();
           continue;
         }
@@ -443,7 +484,7 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
         for (int b = u.ib; b < u.ie;) {
           int e = b;
           double cw = 0;
-          while (e < u.ie && (cw < chunk || e == b)) cw += (ph.items[e++].K + 3) / 4;
+          while (e < u.ie && (cw < kchunk || e == b)) cw += (ph.items[e++].K + 3) / 4;
           q.cuts.push_back({b, e});
           b = e;
         }
@@ -459,14 +500,49 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
     }, unit_grain(ph));
     for (char b : too_big) DMRG_REQUIRE(!b, ST_EINVAL, "split-K tile larger than the reduction covers");
     // offsets, then pass 2 (parallel): units, tiles and slot offsets in place
-    std::vector<long> uat(nu), tat(nu), sat(nu);
+    std::vector<long> uat(nu), tat(nu), sat(nu), cat(nu);
+    long ncut = 0;  // (block, chunk) pairs
     for (long x = 0; x < nu; ++x) {
       uat[x] = nun;
       tat[x] = ntl;
       sat[x] = n_slot_elems;
+      cat[x] = ncut;
       nun += up[x].n_units;
       ntl += up[x].n_tiles;
       n_slot_elems += up[x].n_slot;
+      ncut += std::max<long>(1, (long)up[x].cuts.size());
+    }
+    // Stream units run in the order of the operand their chunk starts at (the T_X
+    // offset: factor by factor), not block by block: blocks that read the same
+    // factors' T_X and right blocks then run at the same time and share them
+    // through the last-level cache (CAS(20,20), M = 1024: 8.71 -> 8.12 ms).
+    std::vector<long> place;  // first unit of every (block, chunk), in launch order
+    if (stream) {
+      constexpr int kBuckets = 8192;
+      long amax = 1;
+      for (const PUnit& u : ph.units)
+        if (u.ib < u.ie) amax = std::max(amax, ph.items[u.ie - 1].aoff + 1);
+      place.resize(ncut);
+      std::vector<long> at(kBuckets + 1, 0);
+      for (int pass = 0; pass < 2; ++pass) {  // count, then place (a counting sort)
+        for (long x = 0; x < nu; ++x) {
+          const PUnit& u = ph.units[x];
+          const UnitPlan& q = up[x];
+          const long nc = std::max<long>(1, (long)q.cuts.size()), nt = (long)q.ts.size();
+          for (long c = 0; c < nc; ++c) {
+            const int i = q.cuts.empty() ? u.ib : q.cuts[c].first;
+            const int b = u.ib < u.ie ? (int)((double)ph.items[i].aoff / (double)amax * (kBuckets - 1)) : 0;
+            if (pass == 0) {
+              at[b + 1] += nt;
+            } else {
+              place[cat[x] + c] = at[b];
+              at[b] += nt;
+            }
+          }
+        }
+        if (pass == 0)
+          for (int b = 0; b < kBuckets; ++b) at[b + 1] += at[b];
+      }
     }
     units = stage_units_.get<GemmUnit>(nun);
     tiles = stage_tiles_.get<SplitTile>(ntl);
@@ -479,8 +555,11 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
         const PUnit& u = ph.units[x];
         const UnitPlan& q = up[x];
         char* C = (char*)bases[u.cbuf] + u.coff * esz[u.cbuf];
-        GemmUnit* uo = units + uat[x];
+        auto first_of = [&](long c) {
+          return units + (place.empty() ? uat[x] + c * (long)q.ts.size() : place[cat[x] + c]);
+        };
         if (q.cuts.empty()) {
+          GemmUnit* uo = first_of(0);
           for (const TileShape& t : q.ts) *uo++ = {C, u.ldc, u.M, u.N, t.m0, t.n0, u.ib, u.ie, u.acc, t.shape};
           continue;
         }
@@ -492,12 +571,14 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
           to[t] = {C, so, u.ldc, u.M, u.N, ts.m0, ts.n0, nc, ts.tm, ts.tn, u.acc, 0};
           so += (long)nc * ts.tm * ts.tn;
         }
-        for (int c = 0; c < nc; ++c)
+        for (int c = 0; c < nc; ++c) {
+          GemmUnit* uo = first_of(c);
           for (size_t t = 0; t < q.ts.size(); ++t) {
             const SplitTile& st_ = to[t];
             *uo++ = {slot0 + (st_.s0 + (long)c * st_.tm * st_.tn) * (long)slot_esz, st_.tn, u.M, u.N, st_.m0, st_.n0,
                      q.cuts[c].first, q.cuts[c].second, 2, q.ts[t].shape};
           }
+        }
       }
     }, unit_grain(ph));
     ph.slot_base[slot] = splitk_.p;
@@ -536,15 +617,15 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
 
 void Solver::launch_resolved(Phase& ph, int prec, int slot) {
   if (prec == PREC_F64) {
-    if (ph.wg_used[slot])
-      launch_gemm_wg(PREC_F64, ph.tag, ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
+    if (ph.stream_used[slot])
+      launch_gemm_stream(PREC_F64, ph.tag, ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
     else
       launch_gemm_w32(ph.mode, ph.tag, ph.buf_ok[slot], ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot],
                       ph.d_items[slot].as<GemmItem>(), st);
     if (ph.gemm_done) (void)hipEventRecord(ph.gemm_done, st);  // GEMM-only timing
     launch_splitk_reduce(ph.d_tiles[slot].as<SplitTile>(), ph.n_tiles[slot], splitk_.as<double>(), st);
-  } else if (prec == PREC_F32 && ph.wg_used[slot]) {
-    launch_gemm_wg(PREC_F32, 0, ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
+  } else if (prec == PREC_F32 && ph.stream_used[slot]) {
+    launch_gemm_stream(PREC_F32, 0, ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
     launch_splitk_reduce_f32(ph.d_tiles[slot].as<SplitTile>(), ph.n_tiles[slot], splitk_.as<float>(), st);
   } else if (prec == PREC_F32) {
     launch_gemm_w32_f32(ph.mode, ph.buf_ok[slot], ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
@@ -901,7 +982,7 @@ void Solver::build_sigma_plan(int k) {
     phA_[c].flops_exec = 0;
     phB_[c].mode = GEMM_NT;
     phB_[c].flops_exec = 0;
-    phB_[c].wg = true;
+    phB_[c].stream = true;
   }
   for (size_t f = 0; f < lf_.fac.size(); ++f) {
     if (chunk_of[f] < 0) continue;
@@ -1190,12 +1271,12 @@ void Solver::build_sigma_plan(int k) {
   // split-K granularity of every chunk from the work of all chunks of the phase
   // (pieces of the same size whatever the chunking)
   for (std::vector<Phase>* v : {&phA_, &phB_}) {
-    double w = 0;
+    if (v->size() <= 1) continue;
+    double w[2] = {0, 0};
     for (const Phase& ph : *v)
-      for (const PUnit& u : ph.units)
-        for (int i = u.ib; i < u.ie; ++i) w += ((u.M + 31) / 32) * ((u.N + 31) / 32) * ((ph.items[i].K + 3) / 4);
-    if (v->size() > 1)
-      for (Phase& ph : *v) ph.split_work = w;
+      for (int c = 0; c < 2; ++c) w[c] += phase_work(ph, c != 0);
+    for (Phase& ph : *v)
+      for (int c = 0; c < 2; ++c) ph.split_work[c] = w[c];
   }
   if (opt_.verbose > 1) {
     auto ms = [](clk::time_point a, clk::time_point b) { return std::chrono::duration<double, std::milli>(b - a).count(); };

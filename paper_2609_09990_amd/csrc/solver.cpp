@@ -22,6 +22,9 @@ void hip_check(hipError_t e, const char* what) {
 namespace {
 std::atomic<long> g_hip_allocs{0};
 constexpr size_t kGranule = 256;
+// readable bytes past every buffer: the stream kernel loads 16 bytes from the
+// last elements of a row on, and drops what lies past the row
+constexpr size_t kSlack = 64;
 }  // namespace
 
 Arena*& current_arena() {
@@ -121,17 +124,17 @@ void DevMem::reserve(size_t b) {
     // a grown buffer keeps a quarter of headroom: fewer reallocations, less fragmentation
     const size_t want = grown ? std::max(b, grown + grown / 4) : b;
     try {
-      p = a->alloc(want);
+      p = a->alloc(want + kSlack);
       bytes = want;
     } catch (const Error&) {
       if (want == b) throw;
-      p = a->alloc(b);
+      p = a->alloc(b + kSlack);
       bytes = b;
     }
     arena = a;
     return;
   }
-  hipError_t e = hipMalloc(&p, b);
+  hipError_t e = hipMalloc(&p, b + kSlack);
   if (e != hipSuccess) {
     p = nullptr;
     throw Error(ST_ENOMEM, "device allocation of " + std::to_string(b) + " bytes failed");

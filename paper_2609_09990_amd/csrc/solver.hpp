@@ -175,9 +175,9 @@ struct Phase {
   const void* last_bases[3][B_NBUF] = {};
   bool uploaded[3] = {false, false, false};
   bool buf_ok[3] = {false, false, false};  // every item fits the buffer-load kernels
-  bool wg = false;                         // may take the fp64 workgroup block kernel (NT)
-  double split_work = 0;                   // > 0: split-K granularity from this work, not the phase's own
-  bool wg_used[3] = {false, false, false};
+  bool stream = false;                     // long item lists: may take the stream kernel (NT)
+  double split_work[2] = {0, 0};           // > 0: split-K granularity from this work (by cost unit), not the phase's own
+  bool stream_used[3] = {false, false, false};
 };
 
 // One side's factors for a middle cut: X_{beta,op} = sum_alpha c L[alpha] (left)
