@@ -23,24 +23,29 @@ bool launch_mlp_infer_bf16(const float* X, long n, int nin, const float* W1, con
                            hipStream_t s);
 void launch_mlp_layer1(const float* X, long n, int nin, const float* W1, const float* b1, int width,
                        float* a1, uint16_t* a1b, hipStream_t s);
-// y[i] = b3 + sum_j max(0, z2[i][j] + b2[j]) W3[j]; if store, z2 <- max(0, z2 + b2).
-void launch_mlp_layer3(float* z2, long n, int width, const float* b2, const float* W3, const float* b3,
-                       float* y, bool store, hipStream_t s);
+// y[i] = b3 + sum_j max(0, z2[i][j] + b2[j]) W3[j].
+void launch_mlp_layer3(const float* z2, long n, int width, const float* b2, const float* W3, const float* b3,
+                       float* y, hipStream_t s);
+// fp32 hidden and output layer: a2 = relu(a1 W2^T + b2) (stored unless null),
+// y = a2 W3^T + b3; part: mlp_layer3_parts(width) x n doubles of scratch.
+int mlp_layer3_parts(int width);
+void launch_mlp_forward_f32(const float* a1, long n, int width, const float* W2, const float* b2, const float* W3,
+                            const float* b3, float* a2, double* part, float* y, hipStream_t s);
+// Their backward from dy: gradients of W1, b1, W2, b2, W3 (overwritten).  Scratch:
+// part of max(2 mlp_row_chunks(n), (nin + 1) mlp_row_tiles(n)) x width doubles,
+// gpart of mlp_row_chunks(n) x width x width floats.
+int mlp_row_tiles(long n);
+int mlp_row_chunks(long n);
+void launch_mlp_backward_f32(const float* X, int nin, const float* a1, const float* a2, const float* dy, long n,
+                             int width, const float* W2, const float* W3, double* part, float* gpart, float* gW1,
+                             float* gb1, float* gW2, float* gb2, float* gW3, hipStream_t s);
 // per segment: [sum y t, sum y y, sum t t] (fp64)
 void launch_seg_stats(const float* y, const float* t, int nseg, int seglen, double* stats, hipStream_t s);
 // d(mean over segments of 1 - cos(y_seg, t_seg))/dy
 void launch_cos_grad(const float* y, const float* t, const double* stats, int nseg, int seglen, float* dy,
                      hipStream_t s);
-// partial[c][j] = sum_{i in chunk c} A[i][j] * (w ? w[i * wstride] : 1)  (fp64 accumulation)
-void launch_colsum_partial(const float* A, long rows, int cols, const float* w, int wstride, long chunk,
-                           double* partial, hipStream_t s);
-// out[j * ostride] = sum_c partial[c][j] (in chunk order)
-void launch_sum_partials(const double* partial, int nchunks, long cols, float* out, int ostride, hipStream_t s);
-void launch_sum_partials_f32(const float* partial, int nchunks, long cols, float* out, hipStream_t s);
-// dz2[i][j] = a2[i][j] > 0 ? dy[i] W3[j] : 0 (in place over a2)
-void launch_mlp_back3(float* a2, const float* dy, const float* W3, long n, int width, hipStream_t s);
-// x[i] = mask[i] > 0 ? x[i] : 0
-void launch_relu_mask(float* x, const float* mask, long n, hipStream_t s);
+// out[0] = sum_{i < n} x[i] (fp64, fixed order); part: mlp_row_chunks(n) doubles
+void launch_sum_all(const float* x, long n, double* part, float* out, hipStream_t s);
 void launch_adam(float* w, float* m, float* v, const float* g, long n, float lr, float b1, float b2, float eps,
                  float c1, float c2, hipStream_t s);
 void launch_f32_to_bf16_rne(const float* x, uint16_t* y, long n, hipStream_t s);
@@ -83,19 +88,18 @@ class MLP {
   long oW1_, ob1_, oW2_, ob2_, oW3_, ob3_;
   hipStream_t st_;
   DevMem p_, m_, v_, grad_, w2b_;
-  DevMem a1_, a1b_, z2_, da1_, y_, dy_, stats_, part_, gpart_;
+  DevMem a1_, a1b_, z2_, y_, dy_, stats_, part_, gpart_;
   int t_ = 0;
-  // cached GEMM tables of the hidden layer
+  // cached GEMM tables of the hidden layer (bf16 inference of other widths)
   struct Tables {
     const void* key[3] = {nullptr, nullptr, nullptr};
     long rows = -1;
-    int mode = -1, prec = -1;
     DevMem du, di;
     std::vector<GemmUnit> hu;
     std::vector<GemmItem> hi;
     int nu = 0;
-  } tz_, tda_, tgw_, ti_;
-  void gemm(Tables& t, int prec, int mode, const void* A, const void* B, void* C, long rows, hipStream_t s);
+  } ti_;
+  void gemm(Tables& t, const void* A, const void* B, void* C, long rows, hipStream_t s);
   void refresh_bf16();
 };
 

@@ -22,7 +22,6 @@ struct SplitMix {
     return std::sqrt(-2.0 * std::log(u1)) * std::cos(6.283185307179586 * u2);
   }
 };
-constexpr long kRowChunk = 512;  // rows per partial of the column reductions and split-K chunks
 }  // namespace
 
 MLP::MLP(int n_in, int width, unsigned long long seed, hipStream_t s) : nin_(n_in), w_(width), st_(s) {
@@ -65,35 +64,19 @@ void MLP::get_params(float* host) const {
   hip_check(hipStreamSynchronize(st_), "mlp params");
 }
 
-// Hidden-layer GEMMs on 64 x 64 tiles.  mode NT: C[rows x W] = A[rows x W] B^T (B = W2);
-// NN: C = A B (B = W2); TN: per chunk of kRowChunk rows a W x W partial A_c^T B_c.
-void MLP::gemm(Tables& t, int prec, int mode, const void* A, const void* B, void* C, long rows, hipStream_t s) {
-  const bool same = t.key[0] == A && t.key[1] == B && t.key[2] == C && t.rows == rows && t.mode == mode &&
-                    t.prec == prec;
-  if (!same) {
+// C[rows x W] = A[rows x W] W2^T (bf16 operands) on 64 x 64 tiles: one item per
+// 64-row tile (the A operand moves with the tile), all W columns.
+void MLP::gemm(Tables& t, const void* A, const void* B, void* C, long rows, hipStream_t s) {
+  if (t.key[0] != A || t.key[1] != B || t.key[2] != C || t.rows != rows) {
     hip_check(hipStreamSynchronize(s), "mlp tables");  // earlier uploads of the staging vectors are done
-    const size_t ea = prec == PREC_BF16 ? 2 : 4, ec = 4;
     t.hu.clear();
     t.hi.clear();
-    if (mode == GEMM_TN) {
-      const long nch = (rows + kRowChunk - 1) / kRowChunk;
-      for (long c = 0; c < nch; ++c) {
-        const long r0 = c * kRowChunk, nr = std::min(kRowChunk, rows - r0);
-        int ib = (int)t.hi.size();
-        t.hi.push_back({(const char*)A + r0 * w_ * ea, (const char*)B + r0 * w_ * ea, w_, w_, (int)nr, 0, 1.0});
-        char* Cc = (char*)C + c * (long)w_ * w_ * ec;
-        for (int m0 = 0; m0 < w_; m0 += 64)
-          for (int n0 = 0; n0 < w_; n0 += 64) t.hu.push_back({Cc, w_, w_, w_, m0, n0, ib, ib + 1, 0});
-      }
-    } else {
-      // one item per 64-row tile (the A operand moves with the tile), all W columns
-      for (long m0 = 0; m0 < rows; m0 += 64) {
-        int ib = (int)t.hi.size();
-        t.hi.push_back({(const char*)A + m0 * w_ * ea, B, w_, w_, w_, 0, 1.0});
-        char* Cm = (char*)C + m0 * w_ * ec;
-        const int M = (int)std::min<long>(64, rows - m0);
-        for (int n0 = 0; n0 < w_; n0 += 64) t.hu.push_back({Cm, w_, M, w_, 0, n0, ib, ib + 1, 0});
-      }
+    for (long m0 = 0; m0 < rows; m0 += 64) {
+      int ib = (int)t.hi.size();
+      t.hi.push_back({(const char*)A + m0 * w_ * 2, B, w_, w_, w_, 0, 1.0});
+      char* Cm = (char*)C + m0 * w_ * 4;
+      const int M = (int)std::min<long>(64, rows - m0);
+      for (int n0 = 0; n0 < w_; n0 += 64) t.hu.push_back({Cm, w_, M, w_, 0, n0, ib, ib + 1, 0});
     }
     t.du.reserve(t.hu.size() * sizeof(GemmUnit) + 64);
     t.di.reserve(t.hi.size() * sizeof(GemmItem) + 64);
@@ -103,11 +86,9 @@ void MLP::gemm(Tables& t, int prec, int mode, const void* A, const void* B, void
     t.key[1] = B;
     t.key[2] = C;
     t.rows = rows;
-    t.mode = mode;
-    t.prec = prec;
     t.nu = (int)t.hu.size();
   }
-  launch_gemm(prec, mode, t.du.as<GemmUnit>(), t.nu, t.di.as<GemmItem>(), s);
+  launch_gemm(PREC_BF16, GEMM_NT, t.du.as<GemmUnit>(), t.nu, t.di.as<GemmItem>(), s);
 }
 
 void MLP::forward(int prec, const float* X, long n, float* y, hipStream_t s) {
@@ -118,17 +99,19 @@ void MLP::forward(int prec, const float* X, long n, float* y, hipStream_t s) {
   if (prec == PREC_BF16 && launch_mlp_infer_bf16(X, n, nin_, P + oW1_, P + ob1_, w_, w2b_.as<uint16_t>(), P + ob2_,
                                                  P + oW3_, P + ob3_, y, s))
     return;
-  z2_.reserve((size_t)n * w_ * 4);
   if (prec == PREC_BF16) {
+    z2_.reserve((size_t)n * w_ * 4);
     a1b_.reserve((size_t)n * w_ * 2);
     launch_mlp_layer1(X, n, nin_, P + oW1_, P + ob1_, w_, nullptr, a1b_.as<uint16_t>(), s);
-    gemm(ti_, PREC_BF16, GEMM_NT, a1b_.p, w2b_.p, z2_.p, n, s);
-  } else {
-    a1_.reserve((size_t)n * w_ * 4);
-    launch_mlp_layer1(X, n, nin_, P + oW1_, P + ob1_, w_, a1_.as<float>(), nullptr, s);
-    gemm(ti_, PREC_F32, GEMM_NT, a1_.p, P + oW2_, z2_.p, n, s);
+    gemm(ti_, a1b_.p, w2b_.p, z2_.p, n, s);
+    launch_mlp_layer3(z2_.as<float>(), n, w_, P + ob2_, P + oW3_, P + ob3_, y, s);
+    return;
   }
-  launch_mlp_layer3(z2_.as<float>(), n, w_, P + ob2_, P + oW3_, P + ob3_, y, false, s);
+  a1_.reserve((size_t)n * w_ * 4);
+  part_.reserve((size_t)mlp_layer3_parts(w_) * n * 8);
+  launch_mlp_layer1(X, n, nin_, P + oW1_, P + ob1_, w_, a1_.as<float>(), nullptr, s);
+  launch_mlp_forward_f32(a1_.as<float>(), n, w_, P + oW2_, P + ob2_, P + oW3_, P + ob3_, nullptr, part_.as<double>(),
+                         y, s);
 }
 
 double MLP::loss_grad(const float* X, const float* T, int nseg, int seglen) {
@@ -138,40 +121,24 @@ double MLP::loss_grad(const float* X, const float* T, int nseg, int seglen) {
   float* G = grad_.as<float>();
   a1_.reserve((size_t)n * w_ * 4);
   z2_.reserve((size_t)n * w_ * 4);
-  da1_.reserve((size_t)n * w_ * 4);
   y_.reserve((size_t)n * 4);
   dy_.reserve((size_t)n * 4);
   stats_.reserve((size_t)nseg * 3 * 8);
-  const int nch = (int)((n + kRowChunk - 1) / kRowChunk);
-  part_.reserve((size_t)nch * std::max<long>(w_, 1) * 8);
+  const long nch = mlp_row_chunks(n), nrt = mlp_row_tiles(n);
+  part_.reserve((size_t)std::max((long)mlp_layer3_parts(w_) * n, std::max(2 * nch, (nin_ + 1) * nrt) * w_) * 8);
   gpart_.reserve((size_t)nch * w_ * w_ * 4);
-  // forward (fp32), keeping a1 and a2
+  // forward (fp32), keeping a1 and a2 (z2_ holds a2)
   launch_mlp_layer1(X, n, nin_, P + oW1_, P + ob1_, w_, a1_.as<float>(), nullptr, st_);
-  gemm(tz_, PREC_F32, GEMM_NT, a1_.p, P + oW2_, z2_.p, n, st_);
-  launch_mlp_layer3(z2_.as<float>(), n, w_, P + ob2_, P + oW3_, P + ob3_, y_.as<float>(), true, st_);
+  launch_mlp_forward_f32(a1_.as<float>(), n, w_, P + oW2_, P + ob2_, P + oW3_, P + ob3_, z2_.as<float>(),
+                         part_.as<double>(), y_.as<float>(), st_);
   // loss and dL/dy
   launch_seg_stats(y_.as<float>(), T, nseg, seglen, stats_.as<double>(), st_);
   launch_cos_grad(y_.as<float>(), T, stats_.as<double>(), nseg, seglen, dy_.as<float>(), st_);
-  // layer 3: dW3 = sum_i dy_i a2_i, db3 = sum_i dy_i
-  launch_colsum_partial(z2_.as<float>(), n, w_, dy_.as<float>(), 1, kRowChunk, part_.as<double>(), st_);
-  launch_sum_partials(part_.as<double>(), nch, w_, G + oW3_, 1, st_);
-  launch_colsum_partial(dy_.as<float>(), n, 1, nullptr, 1, kRowChunk, part_.as<double>(), st_);
-  launch_sum_partials(part_.as<double>(), nch, 1, G + ob3_, 1, st_);
-  // dz2 (in place over a2), dW2 = dz2^T a1, db2 = colsum dz2
-  launch_mlp_back3(z2_.as<float>(), dy_.as<float>(), P + oW3_, n, w_, st_);
-  gemm(tgw_, PREC_F32, GEMM_TN, z2_.p, a1_.p, gpart_.p, n, st_);
-  launch_sum_partials_f32(gpart_.as<float>(), nch, (long)w_ * w_, G + oW2_, st_);
-  launch_colsum_partial(z2_.as<float>(), n, w_, nullptr, 1, kRowChunk, part_.as<double>(), st_);
-  launch_sum_partials(part_.as<double>(), nch, w_, G + ob2_, 1, st_);
-  // da1 = dz2 W2, dz1 = da1 * (a1 > 0); dW1[j][f] = sum_i dz1[i][j] X[i][f], db1 = colsum dz1
-  gemm(tda_, PREC_F32, GEMM_NN, z2_.p, P + oW2_, da1_.p, n, st_);
-  launch_relu_mask(da1_.as<float>(), a1_.as<float>(), n * w_, st_);
-  for (int f = 0; f < nin_; ++f) {
-    launch_colsum_partial(da1_.as<float>(), n, w_, X + f, nin_, kRowChunk, part_.as<double>(), st_);
-    launch_sum_partials(part_.as<double>(), nch, w_, G + oW1_ + f, nin_, st_);
-  }
-  launch_colsum_partial(da1_.as<float>(), n, w_, nullptr, 1, kRowChunk, part_.as<double>(), st_);
-  launch_sum_partials(part_.as<double>(), nch, w_, G + ob1_, 1, st_);
+  // db3 = sum_i dy_i, then everything below it
+  launch_sum_all(dy_.as<float>(), n, part_.as<double>(), G + ob3_, st_);
+  launch_mlp_backward_f32(X, nin_, a1_.as<float>(), z2_.as<float>(), dy_.as<float>(), n, w_, P + oW2_, P + oW3_,
+                          part_.as<double>(), gpart_.as<float>(), G + oW1_, G + ob1_, G + oW2_, G + ob2_, G + oW3_,
+                          st_);
   std::vector<double> hs((size_t)nseg * 3);
   hip_check(hipMemcpyAsync(hs.data(), stats_.p, hs.size() * 8, hipMemcpyDeviceToHost, st_), "loss");
   hip_check(hipStreamSynchronize(st_), "loss");
