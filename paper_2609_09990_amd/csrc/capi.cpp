@@ -7,6 +7,7 @@
 
 #include "../../include/dmrg_mi355x.h"
 #include "capi_guard.hpp"
+#include "ci.hpp"
 #include "mlp.hpp"
 #include "solver.hpp"
 
@@ -14,6 +15,7 @@ using namespace dmrg;
 
 struct dmrg_problem {
   Problem p;
+  mutable CiPool ci;  // tables and scratch of the determinant-space calls
 };
 struct dmrg_solver {
   std::unique_ptr<Arena> arena;  // the attached workspace (outlives s)
@@ -454,7 +456,7 @@ dmrg_status dmrg_ci_rdm12(const dmrg_problem* p, int64_t n, const double* bra, c
   return guard([&] {
     DMRG_REQUIRE(p && bra && ket, ST_EINVAL, "NULL argument");
     require_ci_length(p, n);
-    ci_rdm12(p->p.n, p->p.n_alpha, p->p.n_beta, (hipStream_t)stream, bra, ket, 1.0, gamma, Gamma, overlap);
+    ci_rdm12(&p->ci, p->p.n, p->p.n_alpha, p->p.n_beta, (hipStream_t)stream, bra, ket, 1.0, gamma, Gamma, overlap);
   });
 }
 
@@ -463,7 +465,7 @@ dmrg_status dmrg_ci_apply_v(const dmrg_problem* p, int64_t n, const double* c, d
     DMRG_REQUIRE(p && c && out, ST_EINVAL, "NULL argument");
     require_ci_length(p, n);
     DMRG_REQUIRE(c != out, ST_EINVAL, "out must not alias c");
-    ci_apply_v(p->p.n, p->p.n_alpha, p->p.n_beta, p->p.nq, p->p.B.data(), (hipStream_t)stream, c, out);
+    ci_apply_v(&p->ci, p->p.n, p->p.n_alpha, p->p.n_beta, p->p.nq, p->p.B.data(), (hipStream_t)stream, c, out);
   });
 }
 
@@ -472,7 +474,7 @@ dmrg_status dmrg_ci_rdm3(const dmrg_problem* p, int64_t n, const double* bra, co
   return guard([&] {
     DMRG_REQUIRE(p && bra && ket && Gamma3, ST_EINVAL, "NULL argument");
     require_ci_length(p, n);
-    ci_rdm3(p->p.n, p->p.n_alpha, p->p.n_beta, (hipStream_t)stream, bra, ket, 1.0, Gamma3);
+    ci_rdm3(&p->ci, p->p.n, p->p.n_alpha, p->p.n_beta, (hipStream_t)stream, bra, ket, 1.0, Gamma3);
   });
 }
 
@@ -535,7 +537,7 @@ dmrg_status dmrg_rdm12(dmrg_solver* s, int bra_state, int ket_state, double* gam
     DMRG_REQUIRE(h[0] > 0 && h[1] > 0, ST_ESTATE, "a state has zero norm");
     const double scale = 1.0 / std::sqrt(h[0] * h[1]);
     double ov = 0;
-    ci_rdm12(P.n, P.n_alpha, P.n_beta, s->stream, cb.as<double>(), kv, scale, gamma, Gamma, &ov);
+    ci_rdm12(&s->prob->ci, P.n, P.n_alpha, P.n_beta, s->stream, cb.as<double>(), kv, scale, gamma, Gamma, &ov);
     if (overlap) *overlap = ov * scale;
   });
 }

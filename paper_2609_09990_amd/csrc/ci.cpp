@@ -15,10 +15,9 @@
 //   <bra| E_pq |ket> = <bra | T^ket_{pq}>,
 //   <bra| E_pq E_rs |ket> = <E_qp bra | E_rs ket> = <T^bra_{qp} | T^ket_{rs}>,
 // so one product G = T^bra (T^ket)^T of (n^2 + 1) rows over all determinants
-// gives gamma, Gamma' = <E_pq E_rs> - d_qr gamma_ps and <bra|ket>.  The
-// determinants are taken in passes whose copies fit a fixed budget; G is a
-// split-K sum on the fp64 MFMA block kernel, partial tiles reduced in a fixed
-// order (deterministic), passes added in order.
+// gives gamma, Gamma' = <E_pq E_rs> - d_qr gamma_ps and <bra|ket>.  The copies are
+// formed inside the product (ci_gram.hip); its partial sums over ranges of
+// determinants are added in a fixed order (deterministic).
 #include <algorithm>
 #include <cmath>
 
@@ -54,12 +53,14 @@ std::vector<uint32_t> colex_strings(int n, int k) {
   return out;
 }
 
-// tab[x * N + J] = +-(I + 1) when E_rs |I> = +-|J> (x = r n + s), else 0:
-// a_s removes s from I with (-1)^(electrons below s), a+_r inserts r into what
-// is left with (-1)^(electrons below r).
-std::vector<int> excitation_table(int n, const std::vector<uint32_t>& strs) {
+// The excitation tables of one spin's strings (ci.hpp; `unit`: N_b for alpha, 1 for
+// beta strings): a_s removes s from I with (-1)^(electrons below s), a+_r inserts r
+// into what is left with (-1)^(electrons below r).
+std::vector<int> excitation_table(int n, const std::vector<uint32_t>& strs, long unit, bool identity) {
   const long N = (long)strs.size();
-  std::vector<int> t((long)n * n * N, 0);
+  std::vector<int> rank((size_t)1 << n, -1);
+  for (long J = 0; J < N; ++J) rank[strs[J]] = (int)J;
+  std::vector<int> t(((long)n * n + 2) * N, 0);
   for (long J = 0; J < N; ++J) {
     const uint32_t j = strs[J];
     for (int r = 0; r < n; ++r) {
@@ -69,10 +70,11 @@ std::vector<int> excitation_table(int n, const std::vector<uint32_t>& strs) {
         const uint32_t i = (j & ~(1u << r)) | (1u << s);
         const uint32_t i1 = i & ~(1u << s);
         const int par = popc(i & ((1u << s) - 1)) + popc(i1 & ((1u << r) - 1));
-        const int I = (int)colex_part(i, 0) + 1;
+        const int I = (int)(rank[i] * unit) + 1;
         t[((long)r * n + s) * N + J] = (par & 1) ? -I : I;
       }
     }
+    if (identity) t[(long)n * n * N + J] = (int)(J * unit) + 1;
   }
   return t;
 }
@@ -167,126 +169,195 @@ void gemm_tiles(int mode, const std::vector<GemmItem>& items, const std::vector<
   hip_check(hipStreamSynchronize(st), "ci gemm");
 }
 
-// Split-K product G (M x N, row-major, ldg = N) [+]= sum over chunks g of
-// A_g (M x K_g) B_g^T (N x K_g) on the fp64 MFMA block kernel: A_g = A + g
-// astride, B_g = B + g bstride, both with leading dimension cl; about 2048
-// workgroups, partial tiles reduced in a fixed order; acc adds to G.
-void splitk_nt(const double* A, long astride, const double* B, long bstride, long cl, int M, int N,
-               const std::vector<int>& K, double* G, bool acc, hipStream_t st) {
-  struct Tile {
-    int m0, n0, tm, tn;
-  };
-  std::vector<Tile> tl;
-  for (int m0 = 0; m0 < M; m0 += 96)
-    for (int n0 = 0; n0 < N; n0 += 64)
-      tl.push_back({m0, n0, std::min(96, (M - m0 + 15) / 16 * 16), std::min(64, (N - n0 + 15) / 16 * 16)});
-  const long nt = (long)tl.size(), nch = (long)K.size();
-  std::vector<GemmItem> items;
-  for (long g = 0; g < nch; ++g) {
-    DMRG_REQUIRE(buffer_reach_ok(GEMM_NT, M, N, K[g], (int)cl, (int)cl, 8, 8), ST_EINVAL,
-                 "determinant chunk beyond the block kernel reach");
-    items.push_back({A + g * astride, B + g * bstride, (int)cl, (int)cl, K[g], 0, 1.0});
-  }
-  const long ng = std::max<long>(1, std::min<long>(nch, 2048 / std::max<long>(nt, 1)));
-  std::vector<SplitTile> tiles;
-  std::vector<GemmUnit> units;
-  long so = 0;
-  for (const Tile& t : tl) {
-    tiles.push_back({G, so, N, M, N, t.m0, t.n0, (int)ng, t.tm, t.tn, acc ? 1 : 0, 0});
-    so += ng * t.tm * t.tn;
-  }
-  DevMem slots, ditems, dunits, dtiles;
-  slots.reserve((size_t)so * 8);
-  for (long gi = 0; gi < ng; ++gi) {
-    const int ib = (int)(nch * gi / ng), ie = (int)(nch * (gi + 1) / ng);
-    for (long t = 0; t < nt; ++t) {
-      const SplitTile& s = tiles[t];
-      units.push_back({slots.as<double>() + s.s0 + gi * s.tm * s.tn, s.tn, M, N, s.m0, s.n0, ib, ie, 2,
-                       8 * (s.tm / 16) + s.tn / 16});
+// A checked-out set of tables and scratch: from the problem's pool, or (in a
+// workspace, whose memory must not outlive the call, or without a pool) its own.
+class Work {
+ public:
+  Work(CiPool* pool, int n, int na, int nb, hipStream_t st) : pool_(current_arena() ? nullptr : pool), st_(st) {
+    w_ = pool_ ? pool_->take() : std::make_unique<CiWork>();
+    if (!w_->tables) {
+      const std::vector<uint32_t> sa = colex_strings(n, na), sb = colex_strings(n, nb);
+      const std::vector<int> a = excitation_table(n, sa, (long)sb.size(), true), b = excitation_table(n, sb, 1, false);
+      upload(w_->ta, a, st);
+      upload(w_->tb, b, st);
+      hip_check(hipStreamSynchronize(st), "excitation tables");
+      w_->tables = true;
     }
   }
-  upload(ditems, items, st);
-  upload(dunits, units, st);
-  upload(dtiles, tiles, st);
-  launch_gemm_wg(PREC_F64, 5, dunits.as<GemmUnit>(), (int)units.size(), ditems.as<GemmItem>(), st);
-  launch_splitk_reduce(dtiles.as<SplitTile>(), (int)nt, slots.as<double>(), st);
-  hip_check(hipStreamSynchronize(st), "split-K product");
+  ~Work() {
+    (void)hipStreamSynchronize(st_);  // nothing of this call still uses the set
+    if (pool_) pool_->give(std::move(w_));
+  }
+  Work(const Work&) = delete;
+  Work& operator=(const Work&) = delete;
+  CiWork* operator->() { return w_.get(); }
+
+ private:
+  CiPool* pool_;
+  hipStream_t st_;
+  std::unique_ptr<CiWork> w_;
+};
+
+// G (m x n) of the A and B rows of `src_a`, `src_b` into w->G (one list, src_a and
+// rows `a`, when symmetric).
+void gram(Work& w, int n, bool sym, const double* src_a, std::vector<GramRow> a, const double* src_b, std::vector<GramRow> b,
+          long NA, long NB, hipStream_t st) {
+  GramArgs P{};
+  P.m = (int)a.size();
+  P.n = sym ? P.m : (int)b.size();
+  P.zero = n * n + 1;
+  auto pad = [&](std::vector<GramRow>& v) {
+    while (v.size() % 16) v.push_back({0, P.zero, 0});
+  };
+  pad(a);
+  pad(b);
+  const int ba = (int)a.size() / 16, bb = (int)b.size() / 16;
+  std::vector<GramGroup> groups;
+  std::vector<int2> pairs;
+  int max_pairs = 0, max_rows = 0;
+  if (sym) {
+    DMRG_REQUIRE(ba <= 17, ST_EINVAL, "too many rows of a symmetric product");
+    for (int i = 0; i < ba; ++i)
+      for (int j = 0; j <= i; ++j) pairs.push_back({i, j});
+    groups.push_back({0, 0, 0, (int)pairs.size()});
+    max_pairs = (int)pairs.size();
+    max_rows = 16 * ba;
+  } else {
+    DMRG_REQUIRE(ba <= 17, ST_EINVAL, "too many rows of a product");
+    for (int b0 = 0; b0 < bb; b0 += kGramRows / 16) {
+      const int nb = std::min(kGramRows / 16, bb - b0), p0 = (int)pairs.size();
+      for (int i = 0; i < ba; ++i)
+        for (int j = 0; j < nb; ++j) pairs.push_back({i, j});
+      groups.push_back({16 * b0, 16 * nb, p0, (int)pairs.size() - p0});
+      max_pairs = std::max(max_pairs, ba * nb);
+      max_rows = std::max(max_rows, 16 * (ba + nb));
+    }
+  }
+  P.src_a = src_a;
+  P.src_b = src_b;
+  P.ta = w->ta.as<int>();
+  P.tb = w->tb.as<int>();
+  P.na = (int)NA;
+  P.nb = (int)NB;
+  P.ndet = NA * NB;
+  P.rows_a = 16 * ba;
+  P.sym = sym;
+  // Ranges of determinants: two workgroups per CU for one group of blocks, at most
+  // four rounds of one per CU for many, at least two slices of 32 each.
+  const long slices = (P.ndet + 31) / 32, ng = (long)groups.size();
+  const int nsplit = (int)std::max<long>(1, std::min<long>(ng == 1 ? 512 : std::max<long>(1, 1024 / ng), slices / 2));
+  // tables back to back in one buffer
+  const size_t sa = a.size() * sizeof(GramRow), sb = b.size() * sizeof(GramRow), sg = groups.size() * sizeof(GramGroup),
+               sp = pairs.size() * sizeof(int2);
+  std::vector<char> h(sa + sb + sg + sp);
+  std::copy((const char*)a.data(), (const char*)a.data() + sa, h.data());
+  std::copy((const char*)b.data(), (const char*)b.data() + sb, h.data() + sa);
+  std::copy((const char*)groups.data(), (const char*)groups.data() + sg, h.data() + sa + sb);
+  std::copy((const char*)pairs.data(), (const char*)pairs.data() + sp, h.data() + sa + sb + sg);
+  w->part.reserve((size_t)nsplit * pairs.size() * 256 * 8);
+  w->G.reserve((size_t)P.m * P.n * 8);
+  w->lists.reserve(h.size());
+  hip_check(hipMemcpyAsync(w->lists.p, h.data(), h.size(), hipMemcpyHostToDevice, st), "gram tables");
+  char* d = w->lists.as<char>();
+  P.list_a = (const GramRow*)d;
+  P.list_b = (const GramRow*)(d + sa);
+  P.groups = (const GramGroup*)(d + sa + sb);
+  P.pairs = (const int2*)(d + sa + sb + sg);
+  P.partial = w->part.as<double>();
+  P.G = w->G.as<double>();
+  launch_gram(P, (int)groups.size(), (int)pairs.size(), max_pairs, max_rows, nsplit, st);
+  hip_check(hipStreamSynchronize(st), "gram");  // h is read
 }
 
 }  // namespace
 
 long ci_dimension(int n, int na, int nb) { return binom(n, na) * binom(n, nb); }
 
+std::unique_ptr<CiWork> CiPool::take() {
+  int dev = 0;
+  hip_check(hipGetDevice(&dev), "device");
+  {
+    std::lock_guard<std::mutex> l(m_);
+    for (size_t i = 0; i < idle_.size(); ++i)
+      if (idle_[i]->device == dev) {
+        std::unique_ptr<CiWork> w = std::move(idle_[i]);
+        idle_.erase(idle_.begin() + i);
+        return w;
+      }
+  }
+  auto w = std::make_unique<CiWork>();
+  w->device = dev;
+  return w;
+}
+
+void CiPool::give(std::unique_ptr<CiWork> w) {
+  // the largest buffers go first when the set is over the bound
+  for (;;) {
+    size_t sum = 0;
+    DevMem* big = nullptr;
+    for (DevMem* d : w->scratch()) {
+      sum += d->bytes;
+      if (!big || d->bytes > big->bytes) big = d;
+    }
+    if (sum <= kKeep) break;
+    big->release();
+  }
+  std::lock_guard<std::mutex> l(m_);
+  if (idle_.size() < 2) idle_.push_back(std::move(w));
+}
+
 // V c with V = 1/2 sum_pqrs (pq|rs) E_pq E_rs and (pq|rs) = sum_Q B^Q_pq B^Q_rs,
 // streamed through the factors: T_rs = E_rs c, W_Q = sum_rs B^Q_rs T_rs,
-// U_pq = sum_Q B^Q_pq W_Q, V c = 1/2 sum_pq E_pq U_pq (two GEMMs and two
-// gather kernels; (pq|rs) is never formed).
-void ci_apply_v(int n, int na, int nb, int nq, const double* Bh, hipStream_t st, const double* c, double* out) {
+// U_pq = sum_Q B^Q_pq W_Q (one kernel, T and W on chip), V c = 1/2 sum_pq E_pq
+// U_pq (a gather); (pq|rs) is never formed.
+void ci_apply_v(CiPool* pool, int n, int na, int nb, int nq, const double* Bh, hipStream_t st, const double* c,
+                double* out) {
   DMRG_REQUIRE(n >= 1 && n <= 16 && nq >= 0, ST_EINVAL, "the two-electron operator on CI vectors needs 1..16 orbitals");
-  const std::vector<uint32_t> sa = colex_strings(n, na), sb = colex_strings(n, nb);
-  const long NA = (long)sa.size(), NB = (long)sb.size(), N = NA * NB;
+  const long NA = binom(n, na), NB = binom(n, nb), N = NA * NB;
   const int n2 = n * n;
   if (nq == 0) {
     launch_fill(out, N, 0.0, st);
     hip_check(hipStreamSynchronize(st), "apply V");
     return;
   }
-  DevMem ta, tb, T, W, U, Bd;
-  upload(ta, excitation_table(n, sa), st);
-  upload(tb, excitation_table(n, sb), st);
-  T.reserve((size_t)(n2 + 1) * N * 8);
-  W.reserve((size_t)nq * N * 8);
-  U.reserve((size_t)n2 * N * 8);
-  Bd.reserve((size_t)nq * n2 * 8);
-  hip_check(hipMemcpyAsync(Bd.p, Bh, (size_t)nq * n2 * 8, hipMemcpyHostToDevice, st), "B");
-  launch_ci_excite(c, NA, NB, n2, ta.as<int>(), tb.as<int>(), T.as<double>(), N, 0, N, st);
-  std::vector<GemmItem> items{{Bd.as<double>(), T.as<double>(), n2, (int)N, n2, 0, 1.0}};
-  std::vector<GemmUnit> units;
-  tiles64(units, W.as<double>(), (int)N, nq, (int)N, 0, 1);
-  gemm_tiles(GEMM_NN, items, units, st);  // W = B T (nq x N)
-  items = {{Bd.as<double>(), W.as<double>(), n2, (int)N, nq, 0, 1.0}};
-  units.clear();
-  tiles64(units, U.as<double>(), (int)N, n2, (int)N, 0, 1);
-  gemm_tiles(GEMM_TN, items, units, st);  // U = B^T W (n^2 x N)
-  launch_ci_apply_sum(U.as<double>(), N, NA, NB, n2, ta.as<int>(), tb.as<int>(), 0.5, out, N, st);
+  Work w(pool, n, na, nb, st);
+  w->T1.reserve((size_t)n2 * N * 8);
+  w->F.reserve((size_t)nq * n2 * 8);
+  hip_check(hipMemcpyAsync(w->F.p, Bh, (size_t)nq * n2 * 8, hipMemcpyHostToDevice, st), "B");
+  double* U = w->T1.as<double>();
+  launch_ci_uv(c, (int)NA, (int)NB, n2, nq, w->ta.as<int>(), w->tb.as<int>(), w->F.as<double>(), U, N, st);
+  launch_ci_apply_sum(U, N, NA, NB, n2, w->ta.as<int>(), w->tb.as<int>(), 0.5, out, N, st);
   hip_check(hipStreamSynchronize(st), "apply V");
 }
 
 // Gamma3[pqrstu] = scale <bra|E_pq E_rs E_tu|ket> = scale <E_qp bra | E_rs E_tu ket>:
-// the copies E_tu ket are kept whole, E_rs of each is formed per pass of
-// determinants, and one split-K product of (n^2 + 1) bra rows with n^2 (n^2 + 1)
-// ket rows per pass accumulates G.
-void ci_rdm3(int n, int na, int nb, hipStream_t st, const double* bra, const double* ket, double scale, double* out) {
+// the copies E_qp bra and E_tu ket are kept whole, E_rs of the latter is formed
+// inside one product of n^2 bra rows with the n^2 (n^2 + 1) / 2 ket rows rs >= tu
+// and the n^2 rows E_x ket, which give the others by the commutator.
+void ci_rdm3(CiPool* pool, int n, int na, int nb, hipStream_t st, const double* bra, const double* ket, double scale,
+             double* out) {
   DMRG_REQUIRE(n >= 1 && n <= 12, ST_EINVAL, "the three-body density from CI vectors needs 1..12 orbitals");
-  const std::vector<uint32_t> sa = colex_strings(n, na), sb = colex_strings(n, nb);
-  const long NA = (long)sa.size(), NB = (long)sb.size(), N = NA * NB;
-  const int n2 = n * n, rows = n2 + 1, nbr = n2 * rows;
-  constexpr long CL = 4096;
-  DevMem ta, tb, Tk, T1, T2, G, d3;
-  upload(ta, excitation_table(n, sa), st);
-  upload(tb, excitation_table(n, sb), st);
-  Tk.reserve((size_t)rows * N * 8);
-  launch_ci_excite(ket, NA, NB, n2, ta.as<int>(), tb.as<int>(), Tk.as<double>(), N, 0, N, st);  // [x][N]
-  const long per_pass = std::max<long>(1, (4L << 30) / ((long)nbr * CL * 8)) * CL;
-  const long pass = std::min(per_pass, (N + CL - 1) / CL * CL);
-  T1.reserve((size_t)rows * pass * 8);
-  T2.reserve((size_t)nbr * pass * 8);
-  G.reserve((size_t)rows * nbr * 8);
-  for (long d0 = 0; d0 < N; d0 += pass) {
-    const long dend = std::min(N, d0 + pass), nch = (dend - d0 + CL - 1) / CL;
-    launch_ci_excite(bra, NA, NB, n2, ta.as<int>(), tb.as<int>(), T1.as<double>(), CL, d0, dend, st);
-    // chunk g of E_rs (E_x ket) at T2 + g nbr CL + x rows CL, every x in one launch
-    launch_ci_excite(Tk.as<double>(), NA, NB, n2, ta.as<int>(), tb.as<int>(), T2.as<double>(), CL, d0, dend, st,
-                     (long)nbr * CL, n2, N, (long)rows * CL);
-    std::vector<int> K;
-    for (long g = 0; g < nch; ++g) K.push_back((int)std::min(CL, dend - d0 - g * CL));
-    splitk_nt(T1.as<double>(), rows * CL, T2.as<double>(), (long)nbr * CL, CL, rows, nbr, K, G.as<double>(), d0 > 0,
-              st);
-  }
+  const long NA = binom(n, na), NB = binom(n, nb), N = NA * NB;
+  const int n2 = n * n;
+  Work w(pool, n, na, nb, st);
+  const bool same = bra == ket;
+  w->T2.reserve((size_t)n2 * N * 8);
+  if (!same) w->T1.reserve((size_t)n2 * N * 8);
+  launch_ci_excite(ket, NA, NB, n2, w->ta.as<int>(), w->tb.as<int>(), w->T2.as<double>(), st);
+  if (!same) launch_ci_excite(bra, NA, NB, n2, w->ta.as<int>(), w->tb.as<int>(), w->T1.as<double>(), st);
+  std::vector<GramRow> a, b;
+  for (int x = 0; x < n2; ++x) a.push_back({(long)x * N, n2, 0});
+  // source by source: the rows of a group gather from one to three vectors, which
+  // stay in L1 (excitation by excitation it would be 128)
+  for (int y = 0; y < n2; ++y)
+    for (int x = y; x < n2; ++x) b.push_back({(long)y * N, x, 0});
+  for (int x = 0; x < n2; ++x) b.push_back({(long)x * N, n2, 0});
+  gram(w, n, false, same ? w->T2.as<double>() : w->T1.as<double>(), std::move(a), w->T2.as<double>(), std::move(b), NA, NB,
+       st);
   const long n6 = (long)n2 * n2 * n2;
-  d3.reserve((size_t)n6 * 8);
-  launch_rdm3_assemble(G.as<double>(), nbr, n, rows, scale, d3.as<double>(), st);
-  hip_check(hipMemcpyAsync(out, d3.p, (size_t)n6 * 8, hipMemcpyDeviceToHost, st), "rdm3 out");
+  w->out.reserve((size_t)n6 * 8);
+  launch_rdm3_assemble(w->G.as<double>(), n, scale, w->out.as<double>(), st);
+  hip_check(hipMemcpyAsync(out, w->out.p, (size_t)n6 * 8, hipMemcpyDeviceToHost, st), "rdm3 out");
   hip_check(hipStreamSynchronize(st), "rdm3");
 }
 
@@ -579,39 +650,25 @@ void Solver::mps_to_ci(int state, double* c) {
   hip_check(hipStreamSynchronize(st), "mps_to_ci");
 }
 
-void ci_rdm12(int n, int na, int nb, hipStream_t st, const double* bra, const double* ket, double scale,
+void ci_rdm12(CiPool* pool, int n, int na, int nb, hipStream_t st, const double* bra, const double* ket, double scale,
               double* gamma, double* Gamma, double* overlap) {
   DMRG_REQUIRE(n >= 1 && n <= 16, ST_EINVAL, "RDMs from CI vectors need 1..16 orbitals");
-  const std::vector<uint32_t> sa = colex_strings(n, na), sb = colex_strings(n, nb);
-  const long NA = (long)sa.size(), NB = (long)sb.size(), N = NA * NB;
+  const long NA = binom(n, na), NB = binom(n, nb);
   const int n2 = n * n, rows = n2 + 1;
-  DevMem ta, tb;
-  upload(ta, excitation_table(n, sa), st);
-  upload(tb, excitation_table(n, sb), st);
-  constexpr long CL = 8192;  // determinants per split-K item
-  const long per_pass = std::max<long>(1, (512L << 20) / ((long)rows * CL * 8)) * CL;
-  const long pass = std::min(per_pass, (N + CL - 1) / CL * CL);
+  Work w(pool, n, na, nb, st);
+  std::vector<GramRow> list;
+  for (int x = 0; x < n2; ++x) list.push_back({0, x, 0});
+  list.push_back({0, n2, 0});
   const bool same = bra == ket;
-  DevMem Tb, Tk, G, dg, dG;
-  Tb.reserve((size_t)rows * pass * 8);
-  if (!same) Tk.reserve((size_t)rows * pass * 8);
-  const double* TK = same ? Tb.as<double>() : Tk.as<double>();
-  G.reserve((size_t)rows * rows * 8);
-  for (long d0 = 0; d0 < N; d0 += pass) {
-    const long dend = std::min(N, d0 + pass), nch = (dend - d0 + CL - 1) / CL;
-    launch_ci_excite(bra, NA, NB, n2, ta.as<int>(), tb.as<int>(), Tb.as<double>(), CL, d0, dend, st);
-    if (!same) launch_ci_excite(ket, NA, NB, n2, ta.as<int>(), tb.as<int>(), Tk.as<double>(), CL, d0, dend, st);
-    std::vector<int> K;
-    for (long g = 0; g < nch; ++g) K.push_back((int)std::min(CL, dend - d0 - g * CL));
-    splitk_nt(Tb.as<double>(), rows * CL, TK, rows * CL, CL, rows, rows, K, G.as<double>(), d0 > 0, st);
-  }
-  dg.reserve((size_t)n2 * 8);
-  dG.reserve((size_t)n2 * n2 * 8);
-  launch_rdm_assemble(G.as<double>(), rows, n, scale, dg.as<double>(), dG.as<double>(), st);
-  if (gamma) hip_check(hipMemcpyAsync(gamma, dg.p, (size_t)n2 * 8, hipMemcpyDeviceToHost, st), "rdm out");
-  if (Gamma) hip_check(hipMemcpyAsync(Gamma, dG.p, (size_t)n2 * n2 * 8, hipMemcpyDeviceToHost, st), "rdm out");
+  if (same) gram(w, n, true, bra, list, nullptr, {}, NA, NB, st);
+  else gram(w, n, false, bra, list, ket, list, NA, NB, st);
+  w->out.reserve((size_t)(n2 + (long)n2 * n2) * 8);
+  double *dg = w->out.as<double>(), *dG = dg + n2;
+  launch_rdm_assemble(w->G.as<double>(), rows, n, scale, dg, dG, st);
+  if (gamma) hip_check(hipMemcpyAsync(gamma, dg, (size_t)n2 * 8, hipMemcpyDeviceToHost, st), "rdm out");
+  if (Gamma) hip_check(hipMemcpyAsync(Gamma, dG, (size_t)n2 * n2 * 8, hipMemcpyDeviceToHost, st), "rdm out");
   if (overlap)
-    hip_check(hipMemcpyAsync(overlap, G.as<double>() + (long)n2 * rows + n2, 8, hipMemcpyDeviceToHost, st), "rdm out");
+    hip_check(hipMemcpyAsync(overlap, w->G.as<double>() + (long)n2 * rows + n2, 8, hipMemcpyDeviceToHost, st), "rdm out");
   hip_check(hipStreamSynchronize(st), "rdm");
 }
 

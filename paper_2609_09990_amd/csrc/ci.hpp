@@ -19,6 +19,11 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <memory>
+#include <mutex>
+#include <vector>
+
+#include "solver.hpp"
 
 namespace dmrg {
 
@@ -36,25 +41,81 @@ void launch_ci_scatter(const double* amp, const CiSector* secs, int n_secs, cons
                        const double* ps, const int* sa, const int* sb, const double* ss, double* c, long nb,
                        hipStream_t s);
 
-// Excited copies of a CI vector for determinants [d0, dend), in chunks of cl:
-// T[(g * rows + x) * cl + j] = (E_rs c)[d] for x = r n + s < n2 and c[d] for
-// x = n2 (rows = n2 + 1), d = d0 + g cl + j.  ta[x * na + J] (tb likewise) is
-// +-(I + 1) when E_rs |I> = +-|J> within one spin's strings, 0 when no I.
-// gstride: elements between consecutive chunks (<= 0: (n2 + 1) cl).  nvec source
-// vectors c + v cstride in one launch, written from T + v vstride.
-void launch_ci_excite(const double* c, long na, long nb, int n2, const int* ta, const int* tb, double* T, long cl,
-                      long d0, long dend, hipStream_t s, long gstride = 0, int nvec = 1, long cstride = 0,
-                      long vstride = 0);
+// Excitation tables (N = na nb < 2^31 determinants): for x = r n + s < n2,
+// tb[x * nb + J] is +-(I + 1) when E_rs |I> = +-|J> within the beta strings, 0 when
+// there is no I; ta[x * na + J] is +-(I nb + 1) likewise (I nb: where alpha string
+// I's row starts).  Row n2 is the identity (alpha table: I = J, beta table: none),
+// row n2 + 1 holds zeros.
+//
+// Excited copies of a CI vector: T[x * N + d] = (E_rs c)[d].
+void launch_ci_excite(const double* c, long na, long nb, int n2, const int* ta, const int* tb, double* T,
+                      hipStream_t s);
+// Gram products of excited vectors (ci_gram.hip).  A row: the vector at element
+// offset src of its side's base, excited by row x of the tables.
+struct GramRow {
+  long src;
+  int x, pad;
+};
+// B rows b0 .. b0 + rows_b (a multiple of 16) against every A row; block pairs
+// [p0, p0 + np) of the pair table: (A block, B block of the group).
+struct GramGroup {
+  int b0, rows_b, p0, np;
+};
+struct GramArgs {
+  const double *src_a, *src_b;
+  const GramRow *list_a, *list_b;  // padded with zero rows to multiples of 16
+  const GramGroup* groups;         // ascending p0, back to back
+  const int2* pairs;
+  const int *ta, *tb;
+  int na, nb;
+  long ndet;
+  int zero;         // the tables' row of zeros
+  int rows_a;       // a multiple of 16
+  int m, n;         // rows and columns of G that are wanted
+  int sym;          // A and B are one list: pairs of blocks i >= j, G filled both ways
+  double* partial;  // npairs x nsplit x 256
+  double* G;        // m x n
+};
+constexpr int kGramRows = 128;  // B rows of a group (one list of up to 272 rows when symmetric)
+// max_pairs, max_rows: the largest np and (A and B) rows of a group.
+void launch_gram(const GramArgs& P, int ngroups, int npairs, int max_pairs, int max_rows, int nsplit, hipStream_t s);
+// U[x * N + d] = sum_Q F[Q][x] sum_y F[Q][y] (E_y c)[d] (F row-major nq x n2).
+void launch_ci_uv(const double* c, int na, int nb, int n2, int nq, const int* ta, const int* tb, const double* F,
+                  double* U, long ndet, hipStream_t s);
 // out[d] = scale * sum_{x < n2} (E_x U_x)[d] over the rows U_x = U + x ldu.
 void launch_ci_apply_sum(const double* U, long ldu, long na, long nb, int n2, const int* ta, const int* tb,
                          double scale, double* out, long ndet, hipStream_t s);
-// Gamma3[p q r s t u] = scale G[(q n + p) ldg + (t n + u) rows + r n + s].
-void launch_rdm3_assemble(const double* G, long ldg, int n, int rows, double scale, double* out, hipStream_t s);
+// Gamma3[p q r s t u] = scale <E_qp bra | E_rs E_tu ket> from G (n2 rows E_qp bra;
+// columns: E_rs E_tu ket for X = rs >= Y = tu at Y n2 - Y (Y - 1) / 2 + X - Y, then E_x ket
+// from column n2 (n2 + 1) / 2 on); X < Y by E_rs E_tu = E_tu E_rs + d_st E_ru - d_ru E_ts.
+void launch_rdm3_assemble(const double* G, int n, double scale, double* out, hipStream_t s);
 
 // gamma[pq] = scale G[n2][pq]; Gamma[pqrs] = scale (G[qp][rs] - d_qr G[n2][ps])
 // with G the (n2 + 1) x (n2 + 1) product of the excited copies (row-major, ldg).
 void launch_rdm_assemble(const double* G, int ldg, int n, double scale, double* gamma, double* Gamma,
                          hipStream_t s);
+
+// Device tables and scratch of the determinant-space calls of one problem.  A call
+// checks a set out, uses it alone and gives it back with its work done, so calls
+// from several threads and streams never share one; at most two idle sets are
+// kept, each up to kKeep bytes, until the problem is destroyed.
+struct CiWork {
+  int device = -1;
+  bool tables = false;
+  DevMem ta, tb;              // excitation tables
+  DevMem T1, T2, part, G, out, lists, F;
+  std::vector<DevMem*> scratch() { return {&T1, &T2, &part, &G, &out, &lists, &F}; }
+};
+class CiPool {
+ public:
+  static constexpr size_t kKeep = size_t(2) << 30;
+  std::unique_ptr<CiWork> take();
+  void give(std::unique_ptr<CiWork> w);
+
+ private:
+  std::mutex m_;
+  std::vector<std::unique_ptr<CiWork>> idle_;
+};
 
 // Two-orbital density matrices of a CI vector (unnormalised), for every pair
 // (pairs[2 p], pairs[2 p + 1]), i < j: with the pair's spin orbitals moved to the

@@ -29,32 +29,20 @@ __global__ void ci_scatter_kernel(const double* __restrict__ amp, const CiSector
   }
 }
 
-// blockIdx.y: row x of the copies, blockIdx.z: (source vector v, chunk g) as
-// v nch + g; threads over the chunk.  Consecutive threads take consecutive beta
-// strings of one alpha string, so the alpha-excitation reads are row gathers of
-// c and the beta ones stay in a row.
-__global__ void ci_excite_kernel(const double* __restrict__ c0, long cstride, long na, long nb, int n2,
-                                 const int* __restrict__ ta, const int* __restrict__ tb, double* __restrict__ T,
-                                 long vstride, long nch, long cl, long gstride, long d0, long dend) {
-  const int x = blockIdx.y;
-  const long v = blockIdx.z / nch, g = blockIdx.z - v * nch;
-  const double* __restrict__ c = c0 + v * cstride;
-  double* out = T + v * vstride + g * gstride + (long)x * cl;
-  for (long j = (long)blockIdx.x * blockDim.x + threadIdx.x; j < cl; j += (long)gridDim.x * blockDim.x) {
-    const long d = d0 + g * cl + j;
-    if (d >= dend) break;
+// blockIdx.y: row x of the copies; threads over the determinants.  Consecutive
+// threads take consecutive beta strings of one alpha string, so the alpha
+// excitations read rows of c and the beta ones stay in a row.
+__global__ void ci_excite_kernel(const double* __restrict__ c, long na, long nb, const int* __restrict__ ta,
+                                 const int* __restrict__ tb, double* __restrict__ T) {
+  const long x = blockIdx.y, ndet = na * nb;
+  for (long d = (long)blockIdx.x * blockDim.x + threadIdx.x; d < ndet; d += (long)gridDim.x * blockDim.x) {
     const long ia = d / nb, ib = d - ia * nb;
-    double v;
-    if (x == n2) {
-      v = c[d];
-    } else {
-      v = 0.0;
-      const int xa = ta[(long)x * na + ia];
-      if (xa != 0) v += (xa > 0 ? 1.0 : -1.0) * c[(long)(abs(xa) - 1) * nb + ib];
-      const int xb = tb[(long)x * nb + ib];
-      if (xb != 0) v += (xb > 0 ? 1.0 : -1.0) * c[ia * nb + (abs(xb) - 1)];
-    }
-    out[j] = v;
+    double v = 0.0;
+    const int xa = ta[x * na + ia];
+    if (xa != 0) v += (xa > 0 ? 1.0 : -1.0) * c[abs(xa) - 1 + ib];
+    const int xb = tb[x * nb + ib];
+    if (xb != 0) v += (xb > 0 ? 1.0 : -1.0) * c[ia * nb + (abs(xb) - 1)];
+    T[x * ndet + d] = v;
   }
 }
 
@@ -157,13 +145,10 @@ void launch_ci_scatter(const double* amp, const CiSector* secs, int n_secs, cons
   ci_scatter_kernel<<<dim3(256, n_secs), 256, 0, s>>>(amp, secs, pa, pb, ps, sa, sb, ss, c, nb);
 }
 
-void launch_ci_excite(const double* c, long na, long nb, int n2, const int* ta, const int* tb, double* T, long cl,
-                      long d0, long dend, hipStream_t s, long gstride, int nvec, long cstride, long vstride) {
-  const long nch = (dend - d0 + cl - 1) / cl;
-  if (nch <= 0 || nvec <= 0) return;
-  if (gstride <= 0) gstride = (long)(n2 + 1) * cl;
-  ci_excite_kernel<<<dim3(grid_cap(cl, 64), n2 + 1, (unsigned)(nch * nvec)), 256, 0, s>>>(
-      c, cstride, na, nb, n2, ta, tb, T, vstride, nch, cl, gstride, d0, dend);
+void launch_ci_excite(const double* c, long na, long nb, int n2, const int* ta, const int* tb, double* T,
+                      hipStream_t s) {
+  if (na * nb <= 0 || n2 <= 0) return;
+  ci_excite_kernel<<<dim3(grid_cap(na * nb, 256), n2), 256, 0, s>>>(c, na, nb, ta, tb, T);
 }
 
 // out[d] = scale * sum_{x < n2} (E_x U_x)[d], U_x the rows of U (row-major, ldu).
@@ -173,12 +158,29 @@ __global__ void ci_apply_sum_kernel(const double* __restrict__ U, long ldu, long
   for (long d = (long)blockIdx.x * blockDim.x + threadIdx.x; d < ndet; d += (long)gridDim.x * blockDim.x) {
     const long ia = d / nb, ib = d - ia * nb;
     double v = 0.0;
-    for (int x = 0; x < n2; ++x) {
-      const double* u = U + (long)x * ldu;
-      const int xa = ta[(long)x * na + ia];
-      if (xa != 0) v += (xa > 0 ? 1.0 : -1.0) * u[(long)(abs(xa) - 1) * nb + ib];
-      const int xb = tb[(long)x * nb + ib];
-      if (xb != 0) v += (xb > 0 ? 1.0 : -1.0) * u[ia * nb + (abs(xb) - 1)];
+    // eight excitations at a time, table entries first, then amplitudes (an absent
+    // one reads U_x[d] and drops it): two round trips per eight instead of per one
+    constexpr int UX = 8;
+    for (int x0 = 0; x0 < n2; x0 += UX) {
+      int xa[UX], xb[UX];
+#pragma unroll
+      for (int i = 0; i < UX; ++i) {
+        const long x = x0 + i < n2 ? x0 + i : x0;
+        xa[i] = x0 + i < n2 ? ta[x * na + ia] : 0;
+        xb[i] = x0 + i < n2 ? tb[x * nb + ib] : 0;
+      }
+      double a[UX], b[UX];
+#pragma unroll
+      for (int i = 0; i < UX; ++i) {
+        const double* u = U + (long)(x0 + i < n2 ? x0 + i : x0) * ldu;
+        a[i] = xa[i] != 0 ? u[abs(xa[i]) - 1 + ib] : 0.0;
+        b[i] = xb[i] != 0 ? u[ia * nb + (abs(xb[i]) - 1)] : 0.0;
+      }
+#pragma unroll
+      for (int i = 0; i < UX; ++i) {
+        if (xa[i] != 0) v += xa[i] > 0 ? a[i] : -a[i];
+        if (xb[i] != 0) v += xb[i] > 0 ? b[i] : -b[i];
+      }
     }
     out[d] = scale * v;
   }
@@ -189,20 +191,27 @@ void launch_ci_apply_sum(const double* U, long ldu, long na, long nb, int n2, co
   if (ndet > 0) ci_apply_sum_kernel<<<grid_cap(ndet), 256, 0, s>>>(U, ldu, na, nb, n2, ta, tb, scale, out, ndet);
 }
 
-// Gamma3[((((p n + q) n + r) n + s) n + t) n + u] = scale G[(q n + p) ldg + (t n + u) rows + r n + s]
-__global__ void rdm3_assemble_kernel(const double* __restrict__ G, long ldg, int n, int rows, double scale,
-                                     double* __restrict__ out) {
-  const long n2 = (long)n * n, n6 = n2 * n2 * n2;
+__global__ void rdm3_assemble_kernel(const double* __restrict__ G, int n, double scale, double* __restrict__ out) {
+  const long n2 = (long)n * n, n6 = n2 * n2 * n2, tri = n2 * (n2 + 1) / 2, ldg = tri + n2;
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n6; i += (long)gridDim.x * blockDim.x) {
-    const int u = (int)(i % n), t = (int)(i / n % n), s = (int)(i / n2 % n), r = (int)(i / (n2 * n) % n);
-    const int q = (int)(i / (n2 * n2) % n), p = (int)(i / (n2 * n2 * n));
-    out[i] = scale * G[(long)(q * n + p) * ldg + (long)(t * n + u) * rows + r * n + s];
+    const long Y = i % n2, X = i / n2 % n2, pq = i / (n2 * n2);
+    const int s = (int)(X % n), r = (int)(X / n), u = (int)(Y % n), t = (int)(Y / n);
+    const double* g = G + ((pq % n) * n + pq / n) * ldg;  // row E_qp
+    double v;
+    if (X >= Y) {
+      v = g[Y * n2 - Y * (Y - 1) / 2 + X - Y];
+    } else {
+      v = g[X * n2 - X * (X - 1) / 2 + Y - X];
+      if (s == t) v += g[tri + r * n + u];
+      if (r == u) v -= g[tri + t * n + s];
+    }
+    out[i] = scale * v;
   }
 }
 
-void launch_rdm3_assemble(const double* G, long ldg, int n, int rows, double scale, double* out, hipStream_t s) {
+void launch_rdm3_assemble(const double* G, int n, double scale, double* out, hipStream_t s) {
   const long n2 = (long)n * n;
-  rdm3_assemble_kernel<<<grid_cap(n2 * n2 * n2), 256, 0, s>>>(G, ldg, n, rows, scale, out);
+  rdm3_assemble_kernel<<<grid_cap(n2 * n2 * n2), 256, 0, s>>>(G, n, scale, out);
 }
 
 void launch_rdm_assemble(const double* G, int ldg, int n, double scale, double* gamma, double* Gamma,

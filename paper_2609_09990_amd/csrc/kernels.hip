@@ -4,11 +4,8 @@
 // new environment, or of an intermediate T = X psi) accumulates its block
 // products ("items") in a fixed order with MFMA, so results are bitwise
 // reproducible (no atomics; split-K partial tiles are summed in order by
-// splitk_reduce).  Three shapes:
-//  * gemm_wg: one 256-thread workgroup per unit, tiles up to 96 x 64 covering a
-//    whole output block, A slices staged through LDS and shared by the four
-//    waves, B rows by raw buffer loads, k slices of 32 with one of lookahead
-//    (sigma phase B, fp64 / fp32);
+// splitk_reduce).  Long item lists (sigma phase B, fp64 / fp32) take the stream
+// kernel of gemm_stream.hip; here:
 //  * w32_tile: one wave per (16 RB) x (16 CB) tile reading operands straight
 //    from memory (phase A, environment updates, gradient, fp32 / bf16 forms);
 //  * gemm_f64 / gemm_f32 / gemm_bf16: plain 64 x 64 LDS tiles, four waves of
@@ -590,201 +587,6 @@ __device__ inline float buf_one_f32(__amdgpu_buffer_rsrc_t r, int e) {
   float x;
   __builtin_memcpy(&x, &v, 4);
   return x;
-}
-
-// Block kernel for long item lists in NT mode (fp64 or fp32): one workgroup per unit,
-// whose tile ((16 RB) x (16 CB), up to 96 x 64) covers a whole output block of
-// the sizes a sigma meets, so every item's operands are read once per block
-// rather than once per one-wave tile.  Wave w computes columns 16w .. 16w + 15
-// of all RB row blocks.  A slices (c * A, rows m, k contiguous in memory) are
-// staged through LDS, transposed to As[k][m] and shared by the four waves; each
-// wave reads its own 16 rows of B straight from memory.  LDS holds A as
-// As[m][k], so each lane writes and reads its k pair with one 16-byte LDS op.  Items are walked in
-// k slices of 32 with one slice of lookahead: the next slice's loads are issued
-// before the current slice's MFMAs, and one barrier per slice hands the LDS
-// buffers over.  Requires the buffer-load reach of every item (host-checked).
-constexpr int kWgKs = 32;   // k slice
-constexpr int kWgPk = 34;   // LDS row pitch (elements) of As[m][k]: 16-byte aligned k pairs; 16
-                            // lanes reading rows m..m+15 at one k pair hit 16 distinct 4-bank groups
-
-struct WgStage {
-  int it;  // item index, or -1 past the end
-  int k0;  // first k of the slice
-};
-
-// Element-type specifics of the block kernel: fp64 on v_mfma_f64_16x16x4f64
-// (accumulator element q of lane l: row l/16 + 4q), fp32 on
-// v_mfma_f32_16x16x4f32 (row 4 (l/16) + q); both take A[row l%16][k l/16] and
-// B[k l/16][col l%16] per 4-deep step, so the k pairing is shared.
-template <typename T>
-struct WgType;
-template <>
-struct WgType<double> {
-  typedef v4d acc_t;
-  __device__ static void pair(__amdgpu_buffer_rsrc_t r, int e, double* x) { buf_pair(r, e, x); }
-  __device__ static acc_t mfma(double a, double b, acc_t c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-  __device__ static int row(int kq, int q) { return kq + 4 * q; }
-};
-template <>
-struct WgType<float> {
-  typedef v4f acc_t;
-  __device__ static void pair(__amdgpu_buffer_rsrc_t r, int e, float* x) { buf_pair_f32(r, e, x); }
-  __device__ static acc_t mfma(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-  __device__ static int row(int kq, int q) { return 4 * kq + q; }
-};
-
-// Item descriptors are fetched one item ahead with a vector load (lane l < 10
-// takes dword l) and moved to scalar registers with readlane when used.  A
-// scalar load would share its wait counter with the LDS operations, so every
-// LDS wait of the slice would also wait for the descriptor to come from memory.
-__device__ inline uint32_t desc_word(const GemmItem* items, int j, int lane) {
-  return reinterpret_cast<const uint32_t*>(items + j)[lane < 10 ? lane : 0];
-}
-__device__ inline GemmItem desc_unpack(uint32_t w) {
-  uint32_t d[10];
-#pragma unroll
-  for (int i = 0; i < 10; ++i) d[i] = __builtin_amdgcn_readlane(w, i);
-  GemmItem g;
-  __builtin_memcpy(&g, d, sizeof(GemmItem));
-  return g;
-}
-
-template <typename T, int RB>
-__device__ inline void wg_tile(const GemmUnit& u, const GemmItem* __restrict__ items, T (*As)[96][kWgPk]) {
-  typedef WgType<T> W;
-  typedef typename W::acc_t acc_t;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 15, kq = lane >> 4;
-  const int CB = u.shape & 7;
-  const bool active = wave < CB;  // wave-uniform
-  const int bn = u.n0 + 16 * wave + r;
-  const bool bv = active && bn < u.N;
-  acc_t acc[RB];
-#pragma unroll
-  for (int i = 0; i < RB; ++i) acc[i] = acc_t{};
-  // A staging: 16 RB rows x 16 k-pairs per slice, RB pair loads per thread
-  T sa[RB][2];
-  T sb[4][2];  // this lane's B pairs of the slice: k = k0 + 8 pb + 2 kq (+1)
-  auto load = [&](const GemmItem& g, int k0, T (&xa)[RB][2], T (&xb)[4][2]) {
-    const long ea = (long)(u.M - 1) * g.lda + g.K;
-    const long eb = (long)(u.N - 1) * g.ldb + g.K;
-    const __amdgpu_buffer_rsrc_t ra = buf_rsrc(g.A, ea * (long)sizeof(T)), rb = buf_rsrc(g.B, eb * (long)sizeof(T));
-    // pairs wholly past K are not fetched (their values are never used)
-#pragma unroll
-    for (int j = 0; j < RB; ++j) {
-      const int idx = tid + 256 * j, m = idx >> 4, kp = idx & 15;
-      const int gm = u.m0 + m;
-      const int off = gm < u.M ? gm * g.lda : (int)ea;
-      if (k0 + 2 * kp < g.K) W::pair(ra, off + k0 + 2 * kp, xa[j]);
-    }
-    if (active) {
-      const int off = bv ? bn * g.ldb : (int)eb;
-#pragma unroll
-      for (int pb = 0; pb < 4; ++pb)
-        if (k0 + 8 * pb < g.K) W::pair(rb, off + k0 + 8 * pb + 2 * kq, xb[pb]);
-    }
-  };
-  auto stash = [&](const GemmItem& g, int k0, const T (&xa)[RB][2], int buf) {
-    const T c = (T)g.coef;
-#pragma unroll
-    for (int j = 0; j < RB; ++j) {
-      const int idx = tid + 256 * j, m = idx >> 4, kp = idx & 15;
-      const int k = k0 + 2 * kp;
-      T* dst = &As[buf][m][2 * kp];
-      dst[0] = k < g.K ? xa[j][0] * c : (T)0;
-      dst[1] = k + 1 < g.K ? xa[j][1] * c : (T)0;
-    }
-  };
-  auto next = [&](WgStage s, int K) -> WgStage {
-    if (s.k0 + kWgKs < K) return {s.it, s.k0 + kWgKs};
-    return {s.it + 1 < u.ie ? s.it + 1 : -1, 0};
-  };
-  WgStage cur{u.ib < u.ie ? u.ib : -1, 0};
-  GemmItem g{};     // current item
-  uint32_t qw = 0;  // the next item's descriptor (one dword per lane), fetched one item ahead
-  int buf = 0;
-  if (cur.it >= 0) {
-    g = items[cur.it];
-    load(g, 0, sa, sb);
-    if (cur.it + 1 < u.ie) qw = desc_word(items, cur.it + 1, lane);
-    stash(g, 0, sa, 0);
-  }
-  __syncthreads();
-  while (cur.it >= 0) {
-    const WgStage nx = next(cur, g.K);
-    const bool new_item = nx.it >= 0 && nx.it != cur.it;
-    const GemmItem gn = new_item ? desc_unpack(qw) : g;
-    T na[RB][2], nb[4][2];
-    if (nx.it >= 0) load(gn, nx.k0, na, nb);
-    if (new_item && nx.it + 1 < u.ie) qw = desc_word(items, nx.it + 1, lane);
-    if (active) {
-      // pair blocks of this slice: k = k0 + 8 pb + 2 kq + h, zeroed past K in A
-      const int np = (min(kWgKs, g.K - cur.k0) + 7) >> 3;
-#pragma unroll
-      for (int pb = 0; pb < 4; ++pb) {
-        if (pb < np) {
-          const int kk = 8 * pb + 2 * kq;
-          const bool k0v = cur.k0 + kk < g.K, k1v = cur.k0 + kk + 1 < g.K;
-          const T b0 = (bv && k0v) ? sb[pb][0] : (T)0, b1 = (bv && k1v) ? sb[pb][1] : (T)0;
-          T a[RB][2];
-#pragma unroll
-          for (int i = 0; i < RB; ++i) {
-            const T* src = &As[buf][16 * i + r][kk];
-            a[i][0] = src[0];
-            a[i][1] = src[1];
-          }
-#pragma unroll
-          for (int i = 0; i < RB; ++i) acc[i] = W::mfma(a[i][0], b0, acc[i]);
-#pragma unroll
-          for (int i = 0; i < RB; ++i) acc[i] = W::mfma(a[i][1], b1, acc[i]);
-        }
-      }
-    }
-    if (nx.it >= 0) stash(gn, nx.k0, na, buf ^ 1);
-#pragma unroll
-    for (int pb = 0; pb < 4; ++pb) {
-      sb[pb][0] = nb[pb][0];
-      sb[pb][1] = nb[pb][1];
-    }
-    __syncthreads();
-    buf ^= 1;
-    cur = nx;
-    g = gn;
-  }
-  if (!active) return;
-  T* C = (T*)u.C;
-  const int tn = 16 * CB;
-#pragma unroll
-  for (int i = 0; i < RB; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int tr = 16 * i + W::row(kq, q), tc = 16 * wave + r;
-      const int gm = u.m0 + tr, gn = u.n0 + tc;
-      const T v = acc[i][q];
-      if (u.accumulate == 2) {
-        C[tr * tn + tc] = v;  // partial slot, full tile
-      } else if (gm < u.M && gn < u.N) {
-        const long idx = (long)gm * u.ldc + gn;
-        C[idx] = u.accumulate ? C[idx] + v : v;
-      }
-    }
-}
-
-template <typename T, int TAG>
-__global__ __launch_bounds__(256) void gemm_wg(const GemmUnit* __restrict__ units,
-                                               const GemmItem* __restrict__ items, int n_units) {
-  __shared__ __align__(16) T As[2][96][kWgPk];
-  if ((int)blockIdx.x >= n_units) return;
-  const GemmUnit u = units[blockIdx.x];
-  switch (u.shape >> 3) {  // RB; the tile is (16 RB) x (16 CB), CB = shape & 7
-    case 1: wg_tile<T, 1>(u, items, As); break;
-    case 2: wg_tile<T, 2>(u, items, As); break;
-    case 3: wg_tile<T, 3>(u, items, As); break;
-    case 4: wg_tile<T, 4>(u, items, As); break;
-    case 5: wg_tile<T, 5>(u, items, As); break;
-    default: wg_tile<T, 6>(u, items, As); break;
-  }
 }
 
 // fp32 operands, fp32 accumulation (the precision form): the same one-wave tiles,
@@ -1579,30 +1381,8 @@ void launch_gemm_w32(int mode, int tag, bool buf, const GemmUnit* units, int n_u
 #undef DMRG_W32_LAUNCH
 }
 
-void launch_gemm_wg(int prec, int tag, const GemmUnit* units, int n_units, const GemmItem* items, hipStream_t s) {
-  if (n_units <= 0) return;
-  // unit b on workgroup b: consecutive units (which share operands) run at the
-  // same time on the 8 XCDs in turn; giving each XCD a contiguous eighth of the
-  // list instead measured 1.3x slower for sigma phase B (5.5 -> 7.2 ms), and
-  // runs of 2..32 consecutive units per XCD (list order kept at that grain) no
-  // different (5.37-5.41 ms at CAS(20,20), M = 1024; results bitwise equal)
-  const int grid = n_units;
-  if (prec == PREC_F32) {
-    gemm_wg<float, 0><<<grid, 256, 0, s>>>(units, items, n_units);
-    return;
-  }
-  switch (tag) {
-    case 1: gemm_wg<double, 1><<<grid, 256, 0, s>>>(units, items, n_units); break;
-    case 2: gemm_wg<double, 2><<<grid, 256, 0, s>>>(units, items, n_units); break;
-    case 3: gemm_wg<double, 3><<<grid, 256, 0, s>>>(units, items, n_units); break;
-    case 4: gemm_wg<double, 4><<<grid, 256, 0, s>>>(units, items, n_units); break;
-    case 5: gemm_wg<double, 5><<<grid, 256, 0, s>>>(units, items, n_units); break;
-    default: gemm_wg<double, 0><<<grid, 256, 0, s>>>(units, items, n_units); break;
-  }
-}
-
-// tiles are at most 96 x 64 = 24 chunks of 256 elements
-constexpr int kReduceChunks = 24;
+// tiles are at most 64 x 64 = 16 chunks of 256 elements
+constexpr int kReduceChunks = 16;
 
 void launch_splitk_reduce(const SplitTile* tiles, int n, const double* slots, hipStream_t s) {
   if (n > 0) splitk_reduce<<<dim3(n, kReduceChunks), 256, 0, s>>>(tiles, slots);

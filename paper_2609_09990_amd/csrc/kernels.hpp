@@ -55,7 +55,7 @@ inline bool buffer_reach_ok(int mode, int M, int N, int K, int lda, int ldb, siz
   return ra < lim && rb < lim;
 }
 
-// Output tile (rows m0.., cols n0.. of an M x N block, tm x tn <= 96 x 64
+// Output tile (rows m0.., cols n0.. of an M x N block, tm x tn <= 64 x 64
 // elements) = sum of ns partial tiles (row-major tm x tn each) stored one after
 // another from element s0 of the slot buffer, summed in order; acc = 1 adds
 // that sum to the tile instead.
@@ -72,12 +72,7 @@ void launch_splitk_reduce(const SplitTile* tiles, int n, const double* slots, hi
 // buffers with 64 readable bytes past their end (DevMem's slack); partial tiles
 // (accumulate == 2) are 16 CB wide.
 void launch_gemm_stream(int prec, int tag, const GemmUnit* units, int n_units, const GemmItem* items, hipStream_t s);
-// NT block kernel (prec PREC_F64 or PREC_F32: operands, accumulation and
-// outputs in that type): one 256-thread workgroup per unit, tile (16 RB) x
-// (16 CB) with RB = shape >> 3 in 1..6 and CB = shape & 7 in 1..4; every item
-// must pass buffer_reach_ok.  Partial tiles (accumulate == 2) are 16 CB wide.
-void launch_gemm_wg(int prec, int tag, const GemmUnit* units, int n_units, const GemmItem* items, hipStream_t s);
-// The same for fp32 operands, fp32 accumulation and fp32 outputs and slots.
+// The one-wave kernel for fp32 operands, fp32 accumulation and fp32 outputs and slots.
 void launch_gemm_w32_f32(int mode, bool buf, const GemmUnit* units, int n_units, const GemmItem* items,
                          hipStream_t s);
 void launch_splitk_reduce_f32(const SplitTile* tiles, int n, const float* slots, hipStream_t s);

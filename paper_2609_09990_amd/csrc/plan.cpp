@@ -492,8 +492,8 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
         q.n_units = nc * (long)q.ts.size();
         q.n_tiles = (long)q.ts.size();
         for (const TileShape& ts : q.ts) {
-          // the reduction covers tiles of up to 96 x 64 elements
-          if (ts.tm * ts.tn > 96 * 64) too_big[t] = 1;
+          // the reduction covers tiles of up to 64 x 64 elements
+          if (ts.tm * ts.tn > 64 * 64) too_big[t] = 1;
           q.n_slot += nc * ts.tm * ts.tn;
         }
       }

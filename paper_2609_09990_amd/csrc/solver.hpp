@@ -554,9 +554,13 @@ void fiedler_order(int n, const double* I, int* order, double* fiedler);
 // streamed through the Cholesky factors Bh (host, nq x n x n); and the
 // (transition) three-body density <bra|E_pq E_rs E_tu|ket> (host n^6) of device
 // CI vectors.
-void ci_apply_v(int n, int na, int nb, int nq, const double* Bh, hipStream_t st, const double* c, double* out);
-void ci_rdm3(int n, int na, int nb, hipStream_t st, const double* bra, const double* ket, double scale, double* out);
-void ci_rdm12(int n, int na, int nb, hipStream_t st, const double* bra, const double* ket, double scale,
+// pool: the problem's tables and scratch (ci.hpp); null: none are kept.
+class CiPool;
+void ci_apply_v(CiPool* pool, int n, int na, int nb, int nq, const double* Bh, hipStream_t st, const double* c,
+                double* out);
+void ci_rdm3(CiPool* pool, int n, int na, int nb, hipStream_t st, const double* bra, const double* ket, double scale,
+             double* out);
+void ci_rdm12(CiPool* pool, int n, int na, int nb, hipStream_t st, const double* bra, const double* ket, double scale,
               double* gamma, double* Gamma, double* overlap);
 
 }  // namespace dmrg
