@@ -38,22 +38,57 @@ struct PairClass {
   std::vector<PairBlock> blocks;
   long K = 0;
   std::vector<std::pair<int, int>> prow, qrow;  // (alpha, s'), (beta, s)
-  std::map<std::pair<int, int>, int> prow_of, qrow_of;
+  std::vector<int> prow_of, qrow_of;
 };
 
-int row_index(std::vector<std::pair<int, int>>& rows, std::map<std::pair<int, int>, int>& idx, int ch,
-              int s) {
-  auto key = std::make_pair(ch, s);
-  auto it = idx.find(key);
-  if (it != idx.end()) return it->second;
-  int r = (int)rows.size();
-  rows.push_back(key);
-  idx.emplace(key, r);
-  return r;
+// Host tables of one side's rows, packed for one upload (launch_grad_expand).
+struct GradPlan {
+  std::vector<GradJob> jobs;
+  std::vector<GradTile> tiles;
+  std::vector<GradBlock> blocks;
+  std::vector<GradSrc> srcs;
+  std::vector<GradRow> rows;
+  std::vector<char> packed;
+  long units = 0;
+  double flops = 0;
+  bool buf = true;  // every product fits the buffer-load kernels
+  void clear() { *this = GradPlan(); }
+  template <class T>
+  size_t put(const std::vector<T>& v) {
+    const size_t at = (packed.size() + 15) / 16 * 16;
+    packed.resize(at + v.size() * sizeof(T));
+    if (!v.empty()) std::copy((const char*)v.data(), (const char*)(v.data() + v.size()), packed.data() + at);
+    return at;
+  }
+  size_t at[5] = {0, 0, 0, 0, 0};
+  void pack() {
+    at[0] = put(jobs);
+    at[1] = put(tiles);
+    at[2] = put(blocks);
+    at[3] = put(srcs);
+    at[4] = put(rows);
+  }
+  GradView view(const char* d) const {
+    return {(const GradJob*)(d + at[0]), (const GradTile*)(d + at[1]), (const GradBlock*)(d + at[2]),
+            (const GradSrc*)(d + at[3]), (const GradRow*)(d + at[4]), (int)jobs.size(), units};
+  }
+};
+
+// Index of row (channel ch, state s), added on first use; idx: (channel, state) -> row.
+int row_index(std::vector<std::pair<int, int>>& rows, std::vector<int>& idx, int ch, int s) {
+  const size_t at = 4 * (size_t)ch + s;
+  if (at >= idx.size()) idx.resize(at + 1, -1);
+  if (idx[at] < 0) {
+    idx[at] = (int)rows.size();
+    rows.push_back({ch, s});
+  }
+  return idx[at];
 }
 
 // Largest P or Q chunk, in doubles (two such buffers are live at once).
 constexpr long kChunkElems = 1L << 29;
+// P, Q and G buffers kept between calls, in bytes.
+constexpr size_t kKeepBytes = size_t(1) << 30;
 // K extent of one item of the G = P Q^T product (split-K granule).
 constexpr int kGSplit = 4096;
 
@@ -76,10 +111,9 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
 
   // classes of (i, j') blocks by quantum-number offset; rows each entry needs
   std::vector<PairClass> classes;
-  std::map<std::pair<int, int>, int> class_of;
   auto get_class = [&](QN d) {
-    auto it = class_of.find({d.n, d.sz});
-    if (it != class_of.end()) return it->second;
+    for (size_t c = 0; c < classes.size(); ++c)
+      if (classes[c].delta == d) return (int)c;
     PairClass pc;
     pc.delta = d;
     for (int i = 0; i < (int)bl.sec.size(); ++i) {
@@ -90,7 +124,6 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
     }
     int c = (int)classes.size();
     classes.push_back(std::move(pc));
-    class_of[{d.n, d.sz}] = c;
     return c;
   };
   struct Use { int cls, pr, qr; double w; };
@@ -128,112 +161,189 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
     *norm = 0.0;
   }
 
+  // Products of several classes run together (one launch each for all their P
+  // rows, Q rows and G = P Q^T, one read-back): a site's classes are many and
+  // small, and taken one at a time each cost three plans, six launches and a
+  // synchronisation (243 of them at CAS(12,12), M = 256).
+  // A class whose rows exceed the chunk bound runs by itself in chunks of rows.
+  struct Job {
+    size_t c;
+    int p0, np, q0, nq;
+    long poff, qoff, goff;  // elements of this job's P, Q, G in the buffers
+    bool fresh_p;           // P rows to be formed (not those of the job before)
+  };
+  std::vector<std::vector<double>> Gc(classes.size());
+  std::vector<Job> batch;
+  long bp = 0, bq = 0, bg = 0;
   std::vector<double> Ghost;
+  // The P and Q rows' products (row r, block (i, j'), tile) are made on the device
+  // from tables of the rows and of the blocks: P_{alpha,s'}[i, j'] = L_k[alpha](i, i')
+  // A(i', s', j') and Q_{beta,s}[i, j'] = A(i, s, j) R_{k+1}[beta](j, j').  A row's
+  // channel class fixes its state and sectors, so the tables are (classes) x
+  // (blocks), not (rows) x (blocks); a block without a source is written as zeros.
+  auto make_rows = [&](bool left, GradPlan& gp) {
+    const Env& env = left ? envl : envr;
+    const auto& chans = left ? chl : chr;
+    gp.clear();
+    for (const Job& jb : batch) {
+      const PairClass& pc = classes[jb.c];
+      const int nr = left ? jb.np : jb.nq, r0 = left ? jb.p0 : jb.q0;
+      if (nr == 0 || (left && !jb.fresh_p)) continue;
+      GradJob J{};
+      J.u0 = gp.units;
+      J.out = left ? jb.poff : jb.qoff;
+      J.K = pc.K;
+      J.tile0 = (int)gp.tiles.size();
+      J.blk0 = (int)gp.blocks.size();
+      J.src0 = (int)gp.srcs.size();
+      J.row0 = (int)gp.rows.size();
+      J.nblk = (int)pc.blocks.size();
+      for (int i = 0; i < J.nblk; ++i) {
+        const PairBlock& pb = pc.blocks[i];
+        gp.blocks.push_back({pb.off, pb.mi, pb.mj});
+        for (int m0 = 0; m0 < pb.mi; m0 += 64)
+          for (int n0 = 0; n0 < pb.mj; n0 += 32)
+            gp.tiles.push_back({i, m0, n0, 8 * ((std::min(64, pb.mi - m0) + 15) / 16) + (std::min(32, pb.mj - n0) + 15) / 16});
+      }
+      J.ntile = (int)gp.tiles.size() - J.tile0;
+      std::vector<int> kind_of(env.classes.size(), -1);
+      int kinds = 0;
+      for (int r = 0; r < nr; ++r) {
+        const auto& row = left ? pc.prow[r0 + r] : pc.qrow[r0 + r];
+        const int ch = row.first, st_idx = row.second, cls = env.chan_class[ch];
+        const EnvClass& ec = env.classes[cls];
+        if (kind_of[cls] < 0) {
+          kind_of[cls] = kinds++;
+          for (const PairBlock& pb : pc.blocks) {
+            GradSrc x{0, 0, 0, 0, 0, 0};
+            // sectors of the site block: (ip, s', j') on the left, (i, s, j) on the right
+            const int ip = left ? bl.find(bl.sec[pb.i].q - chans[ch].dq) : pb.i;
+            const int j = left ? pb.j : br.find(bl.sec[pb.i].q + site_qn(st_idx));
+            const int sl = ip < 0 || j < 0 ? -1 : A.lay.slab_of_left[ip];
+            const int ab = sl < 0 ? -1 : A.lay.slabs[sl].block_of(st_idx, j);
+            const int eb = ab < 0 ? -1 : ec.block_of_col[left ? ip : pb.j];
+            if (eb >= 0 && ec.blocks[eb].ri == (left ? pb.i : j)) {
+              const Slab& slab = A.lay.slabs[sl];
+              x.env = ec.blocks[eb].off;
+              x.site = slab.off + slab.blocks[ab].col0;
+              x.K = left ? ec.blocks[eb].mc : br.sec[j].dim;
+              x.lda = left ? ec.blocks[eb].mc : slab.width;
+              x.ldb = left ? slab.width : ec.blocks[eb].mc;
+              x.valid = 1;
+              // host check of what the products read, for this class's last channel
+              const long ea = (long)(pb.mi - 1) * x.lda + x.K, eb2 = (long)(x.K - 1) * x.ldb + pb.mj;
+              DMRG_REQUIRE(x.env + (left ? ea : eb2) <= ec.nnz && x.site + (left ? eb2 : ea) <= A.lay.size, ST_EINVAL,
+                           "gradient plan: operand block out of bounds");
+              gp.buf = gp.buf && buffer_reach_ok(GEMM_NN, pb.mi, pb.mj, x.K, x.lda, x.ldb, 8, 8);
+            }
+            gp.srcs.push_back(x);
+          }
+        }
+        DMRG_REQUIRE(env.chan_off(ch) + ec.nnz <= env.size, ST_EINVAL, "gradient plan: channel out of bounds");
+        gp.rows.push_back({env.chan_off(ch), kind_of[cls], 0});
+        // flops of this row's products
+        const GradSrc* xs = gp.srcs.data() + J.src0 + (long)kind_of[cls] * J.nblk;
+        for (int i = 0; i < J.nblk; ++i)
+          if (xs[i].valid) gp.flops += 2.0 * pc.blocks[i].mi * pc.blocks[i].mj * xs[i].K;
+      }
+      gp.units += (long)nr * J.ntile;
+      gp.jobs.push_back(J);
+    }
+  };
+  auto run_rows = [&](bool left, GradPlan& gp, GradTables& t, double* out) {
+    if (gp.units == 0) return;
+    DMRG_REQUIRE(gp.units < (1L << 31), ST_EINVAL, "too many gradient products in one batch");
+    gp.pack();
+    t.tables.reserve(gp.packed.size());
+    t.units.reserve((size_t)gp.units * sizeof(GemmUnit));
+    t.items.reserve((size_t)gp.units * sizeof(GemmItem));
+    hip_check(hipMemcpyAsync(t.tables.p, gp.packed.data(), gp.packed.size(), hipMemcpyHostToDevice, st), "grad tables");
+    launch_grad_expand(gp.view(t.tables.as<char>()), left, (left ? envl : envr).buf.as<double>(), A.buf.as<double>(),
+                       out, t.units.as<GemmUnit>(), t.items.as<GemmItem>(), st);
+    launch_gemm_w32(GEMM_NN, 0, gp.buf, t.units.as<GemmUnit>(), (int)gp.units, t.items.as<GemmItem>(), st);
+  };
+  auto flush = [&]() {
+    if (batch.empty()) return;
+    // G = P Q^T, K cut into split-K items; the phase's device tables outlive the site
+    Phase& pg = grad_ph_;
+    pg.mode = GEMM_NT;
+    pg.stream = true;
+    pg.items.clear();
+    pg.units.clear();
+    pg.flops = 0;
+    pg.uploaded[0] = false;
+    for (const Job& jb : batch) {
+      const PairClass& pc = classes[jb.c];
+      const int ib = (int)pg.items.size();
+      for (long k0 = 0; k0 < pc.K; k0 += kGSplit) {
+        int kk = (int)std::min<long>(kGSplit, pc.K - k0);
+        pg.items.push_back({B_T, jb.poff + k0, B_OUT, jb.qoff + k0, (int)pc.K, (int)pc.K, kk, 1.0});
+      }
+      pg.units.push_back({B_XMIX, jb.goff, jb.nq, jb.np, jb.nq, 0, 0, ib, (int)pg.items.size(), 0});
+      pg.flops += 2.0 * jb.np * jb.nq * (double)pc.K;
+    }
+    grad_P_.reserve(std::max<long>(bp, 1) * 8);
+    grad_Q_.reserve(std::max<long>(bq, 1) * 8);
+    grad_G_.reserve(std::max<long>(bg, 1) * 8);
+    GradPlan pp, pq;
+    make_rows(true, pp);
+    run_rows(true, pp, grad_tab_[0], grad_P_.as<double>());
+    make_rows(false, pq);
+    run_rows(false, pq, grad_tab_[1], grad_Q_.as<double>());
+    void* bases[B_NBUF] = {};
+    bases[B_T] = grad_P_.p;
+    bases[B_OUT] = grad_Q_.p;
+    bases[B_XMIX] = grad_G_.p;
+    size_t esz[B_NBUF] = {8, 8, 8, 8, 8, 8, 8, 8, 8};
+    long sizes[B_NBUF] = {};
+    sizes[B_T] = bp;
+    sizes[B_OUT] = bq;
+    sizes[B_XMIX] = bg;
+    run_phase(pg, PREC_F64, bases, esz, sizes);
+    Ghost.resize((size_t)bg);
+    hip_check(hipMemcpyAsync(Ghost.data(), grad_G_.p, Ghost.size() * 8, hipMemcpyDeviceToHost, st), "grad G");
+    hip_check(hipStreamSynchronize(st), "grad site");  // the packed tables and staging die here
+    for (const Job& jb : batch) {
+      const int nQ = (int)classes[jb.c].qrow.size();
+      for (int r = 0; r < jb.np; ++r)
+        std::copy(Ghost.begin() + jb.goff + (size_t)r * jb.nq, Ghost.begin() + jb.goff + (size_t)(r + 1) * jb.nq,
+                  Gc[jb.c].begin() + (size_t)(jb.p0 + r) * nQ + jb.q0);
+    }
+    st_.grad_flops += pp.flops + pq.flops + pg.flops;
+    batch.clear();
+    bp = bq = bg = 0;
+  };
   for (size_t c = 0; c < classes.size(); ++c) {
     const PairClass& pc = classes[c];
     if (pc.prow.empty() || pc.K == 0) continue;
     const int nP = (int)pc.prow.size(), nQ = (int)pc.qrow.size();
+    Gc[c].assign((size_t)nP * nQ, 0.0);
     const int cP = (int)std::max<long>(1, std::min<long>(nP, kChunkElems / pc.K));
     const int cQ = (int)std::max<long>(1, std::min<long>(nQ, kChunkElems / pc.K));
-    std::vector<double> Gc((size_t)nP * nQ, 0.0);
-    for (int p0 = 0; p0 < nP; p0 += cP) {
-      const int np = std::min(cP, nP - p0);
-      // P rows: P_{alpha,s'}[i, j'] = L_k[alpha](i, i') A(i', s', j')
-      Phase pp;
-      pp.mode = GEMM_NN;
-      for (int r = 0; r < np; ++r) {
-        const int alpha = pc.prow[p0 + r].first, sp = pc.prow[p0 + r].second;
-        const EnvClass& ec = envl.classes[envl.chan_class[alpha]];
-        const long cbase = envl.chan_off(alpha);
-        for (const PairBlock& pb : pc.blocks) {
-          int ip = bl.find(bl.sec[pb.i].q - chl[alpha].dq);
-          if (ip < 0) continue;
-          int eb = ec.block_of_col[ip];
-          if (eb < 0 || ec.blocks[eb].ri != pb.i) continue;
-          int sl = A.lay.slab_of_left[ip];
-          if (sl < 0) continue;
-          const Slab& slab = A.lay.slabs[sl];
-          int ab = slab.block_of(sp, pb.j);
-          if (ab < 0) continue;
-          int ib = (int)pp.items.size();
-          pp.items.push_back({B_ENVL, cbase + ec.blocks[eb].off, B_PSI, slab.off + slab.blocks[ab].col0,
-                              ec.blocks[eb].mc, slab.width, ec.blocks[eb].mc, 1.0});
-          pp.units.push_back({B_T, (long)r * pc.K + pb.off, pb.mj, pb.mi, pb.mj, 0, 0, ib, ib + 1, 0});
-          pp.flops += 2.0 * pb.mi * ec.blocks[eb].mc * pb.mj;
-        }
-      }
-      grad_P_.reserve(std::max<long>((long)np * pc.K, 1) * 8);
-      launch_fill(grad_P_.as<double>(), (long)np * pc.K, 0.0, st);
-      for (int q0 = 0; q0 < nQ; q0 += cQ) {
-        const int nq = std::min(cQ, nQ - q0);
-        // Q rows: Q_{beta,s}[i, j'] = A(i, s, j) R_{k+1}[beta](j, j')
-        Phase pq;
-        pq.mode = GEMM_NN;
-        for (int r = 0; r < nq; ++r) {
-          const int beta = pc.qrow[q0 + r].first, s = pc.qrow[q0 + r].second;
-          const EnvClass& ec = envr.classes[envr.chan_class[beta]];
-          const long cbase = envr.chan_off(beta);
-          for (const PairBlock& pb : pc.blocks) {
-            int sl = A.lay.slab_of_left[pb.i];
-            if (sl < 0) continue;
-            int j = br.find(bl.sec[pb.i].q + site_qn(s));
-            if (j < 0) continue;
-            const Slab& slab = A.lay.slabs[sl];
-            int ab = slab.block_of(s, j);
-            if (ab < 0) continue;
-            int eb = ec.block_of_col[pb.j];
-            if (eb < 0 || ec.blocks[eb].ri != j) continue;
-            int ib = (int)pq.items.size();
-            pq.items.push_back({B_PSI, slab.off + slab.blocks[ab].col0, B_ENVR, cbase + ec.blocks[eb].off,
-                                slab.width, ec.blocks[eb].mc, br.sec[j].dim, 1.0});
-            pq.units.push_back({B_OUT, (long)r * pc.K + pb.off, pb.mj, pb.mi, pb.mj, 0, 0, ib, ib + 1, 0});
-            pq.flops += 2.0 * pb.mi * br.sec[j].dim * pb.mj;
-          }
-        }
-        // G chunk = P Q^T, K cut into split-K items
-        Phase pg;
-        pg.mode = GEMM_NT;
-        for (long k0 = 0; k0 < pc.K; k0 += kGSplit) {
-          int kk = (int)std::min<long>(kGSplit, pc.K - k0);
-          pg.items.push_back({B_T, k0, B_OUT, k0, (int)pc.K, (int)pc.K, kk, 1.0});
-        }
-        pg.units.push_back({B_XMIX, 0, nq, np, nq, 0, 0, 0, (int)pg.items.size(), 0});
-        pg.flops = 2.0 * np * nq * (double)pc.K;
-        grad_Q_.reserve(std::max<long>((long)nq * pc.K, 1) * 8);
-        grad_G_.reserve(std::max<long>((long)np * nq, 1) * 8);
-        launch_fill(grad_Q_.as<double>(), (long)nq * pc.K, 0.0, st);
-        void* bases[B_NBUF] = {};
-        bases[B_PSI] = A.buf.p;
-        bases[B_ENVL] = envl.buf.p;
-        bases[B_ENVR] = envr.buf.p;
-        bases[B_T] = grad_P_.p;
-        bases[B_OUT] = grad_Q_.p;
-        bases[B_XMIX] = grad_G_.p;
-        size_t esz[B_NBUF] = {8, 8, 8, 8, 8, 8, 8, 8, 8};
-        long sizes[B_NBUF] = {};
-        sizes[B_PSI] = A.lay.size;
-        sizes[B_ENVL] = envl.size;
-        sizes[B_ENVR] = envr.size;
-        sizes[B_T] = (long)np * pc.K;
-        sizes[B_OUT] = (long)nq * pc.K;
-        sizes[B_XMIX] = (long)np * nq;
-        if (q0 == 0) run_phase(pp, PREC_F64, bases, esz, sizes);
-        run_phase(pq, PREC_F64, bases, esz, sizes);
-        run_phase(pg, PREC_F64, bases, esz, sizes);
-        Ghost.resize((size_t)np * nq);
-        hip_check(hipMemcpyAsync(Ghost.data(), grad_G_.p, Ghost.size() * 8, hipMemcpyDeviceToHost, st), "grad G");
-        hip_check(hipStreamSynchronize(st), "grad site");  // local plans and staging die here
-        for (int r = 0; r < np; ++r)
-          for (int t = 0; t < nq; ++t) Gc[(size_t)(p0 + r) * nQ + q0 + t] = Ghost[(size_t)r * nq + t];
-        st_.grad_flops += (q0 == 0 ? pp.flops : 0.0) + pq.flops + pg.flops;
-      }
+    if (cP == nP && cQ == nQ) {
+      const long np = (long)nP * pc.K, nq = (long)nQ * pc.K;
+      if (bp + np > kChunkElems || bq + nq > kChunkElems) flush();
+      batch.push_back({c, 0, nP, 0, nQ, bp, bq, bg, true});
+      bp += np;
+      bq += nq;
+      bg += (long)nP * nQ;
+      continue;
     }
-    for (size_t e = 0; e < W.size(); ++e)
-      for (const Use& u : uses[e])
-        if (u.cls == (int)c) g[e] += u.w * Gc[(size_t)u.pr * nQ + u.qr];
-    for (const Use& u : norm_uses)
-      if (u.cls == (int)c) *norm += Gc[(size_t)u.pr * nQ + u.qr];
+    flush();
+    for (int p0 = 0; p0 < nP; p0 += cP)
+      for (int q0 = 0; q0 < nQ; q0 += cQ) {
+        const int np = std::min(cP, nP - p0), nq = std::min(cQ, nQ - q0);
+        batch.push_back({c, p0, np, q0, nq, 0, 0, 0, q0 == 0});
+        bp = (long)np * pc.K;
+        bq = (long)nq * pc.K;
+        bg = (long)np * nq;
+        flush();
+      }
   }
+  flush();
+  for (size_t e = 0; e < W.size(); ++e)
+    for (const Use& u : uses[e]) g[e] += u.w * Gc[u.cls][(size_t)u.pr * (int)classes[u.cls].qrow.size() + u.qr];
+  for (const Use& u : norm_uses) *norm += Gc[u.cls][(size_t)u.pr * (int)classes[u.cls].qrow.size() + u.qr];
 }
 
 // Per root r with weight w_r != 0: E_r = <Psi_r|H|Psi_r>/<Psi_r|Psi_r> + e_core and
@@ -290,18 +400,27 @@ void Solver::grad(const std::vector<double>& w, std::vector<double>& dh, std::ve
   }
   // (pq|rs) = sum_Q B^Q_pq B^Q_rs:  dE/dB^Q_ij += sum_rs (dg_ijrs + dg_rsij) B^Q_rs
   const size_t n2 = (size_t)n * n;
+  std::vector<double> sym(dg.size()), acc(n2);
+  for (size_t ij = 0; ij < n2 && nq > 0; ++ij)
+    for (size_t rs = 0; rs < n2; ++rs) sym[rs * n2 + ij] = dg[ij * n2 + rs] + dg[rs * n2 + ij];
   for (int q = 0; q < nq; ++q) {
     const double* Bq = prob_->B.data() + (size_t)q * n2;
     double* out = dB.data() + (size_t)q * n2;
-    for (size_t ij = 0; ij < n2; ++ij) {
-      double acc = 0.0;
-      for (size_t rs = 0; rs < n2; ++rs) acc += (dg[ij * n2 + rs] + dg[rs * n2 + ij]) * Bq[rs];
-      out[ij] += acc;
-    }
+    std::fill(acc.begin(), acc.end(), 0.0);
+    for (size_t rs = 0; rs < n2; ++rs)
+      for (size_t ij = 0; ij < n2; ++ij) acc[ij] += sym[rs * n2 + ij] * Bq[rs];
+    for (size_t ij = 0; ij < n2; ++ij) out[ij] += acc[ij];
   }
-  grad_P_.release();
-  grad_Q_.release();
-  grad_G_.release();
+  // small buffers stay for the next call; a workspace gets everything back
+  size_t kept = grad_P_.bytes + grad_Q_.bytes + grad_G_.bytes;
+  for (const GradTables& t : grad_tab_) kept += t.tables.bytes + t.units.bytes + t.items.bytes;
+  if (current_arena() || kept > kKeepBytes) {
+    grad_P_.release();
+    grad_Q_.release();
+    grad_G_.release();
+    for (GradTables& t : grad_tab_) t = GradTables();
+    grad_ph_ = Phase();
+  }
   st_.grad_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
 }
 

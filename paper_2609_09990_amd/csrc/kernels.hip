@@ -931,6 +931,32 @@ __global__ __launch_bounds__(256) void gemm_bf16_w32(const GemmUnit* __restrict_
   }
 }
 
+// One thread per unit.  Planned on the host, the gradient's 330 thousand row
+// products at CAS(12,12), M = 256 took 40 ms to list, check and upload against 7 ms
+// of kernels; their tables (channel classes x blocks) are a few thousand entries.
+// Energy and gradient of a given MPS there: 106 -> 25 ms (with the classes of a
+// site in one launch and the long-K product on the stream kernel).
+__global__ void grad_expand_kernel(GradView v, int left, const double* env, const double* site, double* out,
+                                   GemmUnit* __restrict__ units, GemmItem* __restrict__ items) {
+  for (long u = (long)blockIdx.x * blockDim.x + threadIdx.x; u < v.units; u += (long)gridDim.x * blockDim.x) {
+    int a = 0, b = v.n_jobs - 1;  // the last job with u0 <= u
+    while (a < b) {
+      const int m = (a + b + 1) / 2;
+      if (v.jobs[m].u0 <= u) a = m;
+      else b = m - 1;
+    }
+    const GradJob J = v.jobs[a];
+    const long r = (u - J.u0) / J.ntile;
+    const GradTile t = v.tiles[J.tile0 + (u - J.u0 - r * J.ntile)];
+    const GradBlock bk = v.blocks[J.blk0 + t.block];
+    const GradRow row = v.rows[J.row0 + r];
+    const GradSrc x = v.srcs[J.src0 + (long)row.kind * J.nblk + t.block];
+    const double *e = env + row.chan + x.env, *s = site + x.site;
+    items[u] = {left ? e : s, left ? s : e, x.lda, x.ldb, x.K, 0, 1.0};
+    units[u] = {out + J.out + r * J.K + bk.off, bk.mj, bk.mi, bk.mj, t.m0, t.n0, (int)u, (int)u + x.valid, 0, t.shape};
+  }
+}
+
 __global__ void splitk_reduce_f32(const SplitTile* __restrict__ tiles, const float* __restrict__ slots) {
   // workgroup (tile, chunk of 256 elements): one element per thread
   const SplitTile t = tiles[blockIdx.x];
@@ -1379,6 +1405,12 @@ void launch_gemm_w32(int mode, int tag, bool buf, const GemmUnit* units, int n_u
     default: DMRG_W32_LAUNCH(0) break;
   }
 #undef DMRG_W32_LAUNCH
+}
+
+void launch_grad_expand(const GradView& v, bool left, const double* env, const double* site, double* out,
+                        GemmUnit* units, GemmItem* items, hipStream_t s) {
+  if (v.units > 0)
+    grad_expand_kernel<<<grid_for(v.units), 256, 0, s>>>(v, left ? 1 : 0, env, site, out, units, items);
 }
 
 // tiles are at most 64 x 64 = 16 chunks of 256 elements

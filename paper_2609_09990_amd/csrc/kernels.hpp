@@ -55,6 +55,44 @@ inline bool buffer_reach_ok(int mode, int M, int N, int K, int lda, int ldb, siz
   return ra < lim && rb < lim;
 }
 
+// Row products of the integral gradient (grad.cpp), expanded into units and items
+// on the device.  A job's rows (channels) all have the blocks blk0 .. blk0 + nblk
+// and the tiles tile0 .. tile0 + ntile; row r's blocks start at out + r K of the
+// output.  srcs[src0 + kind nblk + b]: block b's operands for the rows of a kind
+// (env relative to the row's channel); unit u = u0 + r ntile + tile, item u (none
+// where the block has no source: zeros are written).
+struct GradJob {
+  long u0, out, K;
+  int ntile, tile0, blk0, nblk, src0, row0;
+};
+struct GradTile {
+  int block, m0, n0, shape;
+};
+struct GradBlock {
+  long off;
+  int mi, mj;
+};
+struct GradSrc {
+  long env, site;
+  int K, lda, ldb, valid;
+};
+struct GradRow {
+  long chan;
+  int kind, pad;
+};
+struct GradView {
+  const GradJob* jobs;
+  const GradTile* tiles;
+  const GradBlock* blocks;
+  const GradSrc* srcs;
+  const GradRow* rows;
+  int n_jobs;
+  long units;
+};
+// left: A = env block, B = site block; right: A = site block, B = env block.
+void launch_grad_expand(const GradView& v, bool left, const double* env, const double* site, double* out,
+                        GemmUnit* units, GemmItem* items, hipStream_t s);
+
 // Output tile (rows m0.., cols n0.. of an M x N block, tm x tn <= 64 x 64
 // elements) = sum of ns partial tiles (row-major tm x tn each) stored one after
 // another from element s0 of the slot buffer, summed in order; acc = 1 adds

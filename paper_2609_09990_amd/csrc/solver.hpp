@@ -495,6 +495,11 @@ class Solver {
   void gemm_once(int mode, std::vector<GemmItem>& items, std::vector<GemmUnit>& units);
   void grad_site(int k, std::vector<double>& g, double* norm);
   DevMem grad_P_, grad_Q_, grad_G_;
+  struct GradTables {
+    DevMem tables, units, items;
+  };
+  GradTables grad_tab_[2];  // P and Q rows of one batch of classes (grad.cpp)
+  Phase grad_ph_;           // their product
 
   // learned preconditioner and training-triple store
   bool last_converged_ = true;
