@@ -1081,6 +1081,27 @@ __global__ void dots_final(const double* __restrict__ partial, int nchunk, doubl
   if (threadIdx.x == 0) out[i] = red[0];
 }
 
+// dots of short vectors in one launch (one workgroup per vector): n <= kDotsOne
+// elements take less time than the second launch of the two-pass form.
+constexpr long kDotsOne = 16384;
+__global__ __launch_bounds__(512) void dots_one(const double* __restrict__ V, long ldv, const double* __restrict__ x,
+                                                long n, double* __restrict__ out) {
+  const double* v = V + (long)blockIdx.x * ldv;
+  double acc = 0.0;
+#pragma unroll 4
+  for (long j = threadIdx.x; j < n; j += 512) acc += v[j] * x[j];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  __shared__ double red[8];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = red[0];
+    for (int w = 1; w < 8; ++w) s += red[w];
+    out[blockIdx.x] = s;
+  }
+}
+
 __global__ void gemv_kernel(const double* __restrict__ V, long ldv, int k,
                             const double* __restrict__ coef, double alpha, double* __restrict__ out,
                             double beta, long n) {
@@ -1165,33 +1186,46 @@ __global__ void add_squares_kernel(double* __restrict__ d, const double* __restr
 // iteration ends when no pair is significant (a sweep would rotate nothing) or
 // the off-diagonal part is at the rounding level.
 __device__ inline void jacobi_pair(int round, int t, int n, int& p, int& q) {
+  int x, y;  // 0 <= round, t < n - 1
   if (t == 0) {
-    p = round % (n - 1);
-    q = n - 1;
+    x = round;
+    y = n - 1;
   } else {
-    p = (round + t) % (n - 1);
-    q = (round - t + (n - 1)) % (n - 1);
+    x = round + t;
+    if (x >= n - 1) x -= n - 1;
+    y = round - t;
+    if (y < 0) y += n - 1;
   }
-  if (p > q) {
-    const int x = p;
-    p = q;
-    q = x;
-  }
+  p = min(x, y);
+  q = max(x, y);
 }
 __device__ inline bool jacobi_significant(double apq, double app, double aqq) {
-  return fabs(apq) > 1e-300 && fabs(apq) > 1e-15 * sqrt(fabs(app * aqq));
+  return fabs(apq) > 1e-300 && fabs(apq) > 1e-15 * __builtin_amdgcn_sqrt(fabs(app * aqq));
 }
-// rotation of pair (p, q), p < q < k: c = 1, s = 0 when the coupling is not significant
+// rotation of pair (p, q), p < q < k: c = 1, s = 0 when the coupling is not
+// significant.  t = tan of the angle from hardware estimates and one Newton step
+// (an inexact angle leaves a coupling of its relative error for the next sweep);
+// c = 1 / sqrt(1 + t^2) to full precision and s = t c, so the rotation is
+// orthogonal to rounding.  The exact divisions and roots, a chain of five, took
+// most of a round (125 us per call at k = 32).
 __device__ inline void jacobi_angle(const double (*A)[65], int p, int q, double& c, double& s) {
-  c = 1.0;
-  s = 0.0;
   const double apq = A[p][q], app = A[p][p], aqq = A[q][q];
-  if (jacobi_significant(apq, app, aqq)) {
-    const double theta = (aqq - app) / (2.0 * apq);
-    const double tt = (theta >= 0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-    c = 1.0 / sqrt(tt * tt + 1.0);
-    s = tt * c;
-  }
+  const bool rot = jacobi_significant(apq, app, aqq);
+  double x = aqq - app, y = 2.0 * apq;
+  const double m = fmax(fabs(x), fabs(y));
+  const double sc = m < 0x1p-460 ? 0x1p500 : (m > 0x1p460 ? 0x1p-500 : 1.0);  // keeps h in range
+  x *= sc;
+  y *= sc;
+  const double h = fma(x, x, y * y);
+  const double g = __builtin_amdgcn_rsq(h), r0 = h * g, r = fma(0.5 * g, fma(-r0, r0, h), r0);
+  const double den = fabs(x) + r, i0 = __builtin_amdgcn_rcp(den), inv = i0 * fma(-den, i0, 2.0);
+  const double t = (x >= 0.0 ? y : -y) * inv, w = fma(t, t, 1.0);
+  double cc = __builtin_amdgcn_rsq(w);
+  cc *= fma(-0.5 * w * cc, cc, 1.5);
+  cc *= fma(-0.5 * w * cc, cc, 1.5);
+  cc = fma(0.5 * cc, fma(-w * cc, cc, 1.0), cc);
+  c = rot ? cc : 1.0;
+  s = rot ? t * cc : 0.0;
 }
 
 __global__ __launch_bounds__(256) void jacobi_eig_kernel(const double* __restrict__ G, int ldg, int k,
@@ -1199,7 +1233,7 @@ __global__ __launch_bounds__(256) void jacobi_eig_kernel(const double* __restric
                                                          double* __restrict__ evecs) {
   __shared__ double A[2][64][65];
   __shared__ double V[2][64][65];
-  __shared__ double red[3][256];
+  __shared__ double red[2][3][4];
   __shared__ int order[64];
   const int t = threadIdx.x;
   for (int e = t; e < k * k; e += blockDim.x) {  // lower triangle holds the matrix
@@ -1210,6 +1244,13 @@ __global__ __launch_bounds__(256) void jacobi_eig_kernel(const double* __restric
   __syncthreads();
   const int n = k + (k & 1);
   const int half = n / 2;
+  int ba[4], bb[4];  // this thread's blocks of a round
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int e = t + 256 * i;
+    ba[i] = e < half * half ? e / half : -1;
+    bb[i] = e - (ba[i] < 0 ? 0 : ba[i]) * half;
+  }
   int cur = 0;
   for (int sweep = 0; sweep < 40 && k > 1; ++sweep) {
     double off = 0.0, dg = 0.0, sig = 0.0;
@@ -1220,31 +1261,34 @@ __global__ __launch_bounds__(256) void jacobi_eig_kernel(const double* __restric
       else dg += a * a;
       if (i < j && jacobi_significant(a, A[cur][i][i], A[cur][j][j])) sig += 1.0;
     }
-    red[0][t] = off;
-    red[1][t] = dg;
-    red[2][t] = sig;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (t < s) {
-        red[0][t] += red[0][t + s];
-        red[1][t] += red[1][t + s];
-        red[2][t] += red[2][t + s];
-      }
-      __syncthreads();
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      off += __shfl_xor(off, o, 64);
+      dg += __shfl_xor(dg, o, 64);
+      sig += __shfl_xor(sig, o, 64);
     }
-    const double offsum = red[0][0], dgsum = red[1][0], nsig = red[2][0];
-    __syncthreads();  // red is written again by the next sweep's check
+    double(*rd)[4] = red[sweep & 1];  // two copies: the next check writes the other one
+    if ((t & 63) == 0) {
+      rd[0][t >> 6] = off;
+      rd[1][t >> 6] = dg;
+      rd[2][t >> 6] = sig;
+    }
+    __syncthreads();
+    const double offsum = (rd[0][0] + rd[0][1]) + (rd[0][2] + rd[0][3]);
+    const double dgsum = (rd[1][0] + rd[1][1]) + (rd[1][2] + rd[1][3]);
+    const double nsig = (rd[2][0] + rd[2][1]) + (rd[2][2] + rd[2][3]);
     if (nsig == 0.0 || offsum <= 1e-32 * (dgsum > 1e-300 ? dgsum : 1e-300)) break;  // uniform
     for (int round = 0; round < n - 1; ++round) {
       const double(*Ai)[65] = A[cur];
       const double(*Vi)[65] = V[cur];
       double(*Ao)[65] = A[cur ^ 1];
       double(*Vo)[65] = V[cur ^ 1];
-      for (int e = t; e < half * half; e += blockDim.x) {
-        const int a = e / half, b = e % half;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (ba[i] < 0) continue;
         int pa, qa, pb, qb;
-        jacobi_pair(round, a, n, pa, qa);
-        jacobi_pair(round, b, n, pb, qb);
+        jacobi_pair(round, ba[i], n, pa, qa);
+        jacobi_pair(round, bb[i], n, pb, qb);
         const bool va = qa < k, vb = qb < k;  // false: the pair holds the padding index
         double ca = 1.0, sa = 0.0, cb = 1.0, sb = 0.0;
         if (va) jacobi_angle(Ai, pa, qa, ca, sa);
@@ -1512,6 +1556,10 @@ void launch_fill_f32(float* x, long n, hipStream_t s) {
 void launch_dots(const double* V, long ldv, int k, const double* x, long n, double* partial,
                  double* out, hipStream_t s) {
   if (k <= 0) return;
+  if (n <= kDotsOne) {
+    dots_one<<<k, 512, 0, s>>>(V, ldv, x, n, out);
+    return;
+  }
   long chunk = 8192;
   int nchunk = (int)((n + chunk - 1) / chunk);
   if (nchunk > 512) {
