@@ -110,9 +110,22 @@ void launch_splitk_reduce(const SplitTile* tiles, int n, const double* slots, hi
 // buffers with 64 readable bytes past their end (DevMem's slack); partial tiles
 // (accumulate == 2) are 16 CB wide.
 void launch_gemm_stream(int prec, int tag, const GemmUnit* units, int n_units, const GemmItem* items, hipStream_t s);
-// The one-wave kernel for fp32 operands, fp32 accumulation and fp32 outputs and slots.
-void launch_gemm_w32_f32(int mode, bool buf, const GemmUnit* units, int n_units, const GemmItem* items,
-                         hipStream_t s);
+// Slab kernel (gemm_slab.hip): T_f = X_f B for the factors f of one block shape.  Job
+// job0 + f: X_f (M x K, row-major, row stride K) and T_f (row stride ldt; fp64 for
+// PREC_F64, fp32 otherwise).  A unit computes rows [row0, row1) of the factors' rows
+// stacked (row f M + m) and columns n0 .. n0 + N (at most 64): B points at column n0
+// of a K x .. row-major operand.  X is read up to 15 bytes past its last element.
+struct SlabJob {
+  const void* X;
+  void* T;
+};
+struct SlabUnit {
+  const void* B;
+  int ldb, K, M, N, ldt, n0, job0, row0, row1;
+};
+// tall: 256 rows a step per workgroup (eight waves of 32), strips of 64 k's in LDS;
+// otherwise 64 rows (four waves of 16) and 16 k's.
+void launch_gemm_slab(int prec, bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs, hipStream_t s);
 void launch_splitk_reduce_f32(const SplitTile* tiles, int n, const float* slots, hipStream_t s);
 // bf16 one-wave variant: A bf16 bits (a_f32 = false) or fp32 rounded to bf16,
 // B bf16 bits, fp32 accumulation and fp32 outputs / slots.

@@ -346,7 +346,97 @@ static bool validate_phase(const Phase& ph, const long* sizes, const size_t* esz
   return ok;
 }
 
+void Solver::stage_sent() {
+  if (!stage_ev_) hip_check(hipEventCreateWithFlags(&stage_ev_, hipEventDisableTiming), "staging event");
+  hip_check(hipEventRecord(stage_ev_, st), "staging event");
+  stage_pending_ = true;
+}
+
+// Slab phases: each run's stacked rows in strips of at most 64 columns and ranges of
+// rows, about kSlabUnits units and at least one step each (phase A at CAS(20,20),
+// M = 1024: 1.82 ms with 4096, 1.74 with 8192; CAS(12,12), M = 512: 307 and 310 us).
+// Short phases of shallow blocks (fewer than kSlabTall stacked rows, every K <= 16)
+// take the flat form, whose units hold 20 KB of LDS and are all resident: CAS(8,8),
+// M = 60, 105 thousand rows: 9.5 us, 13 to 15 in the tall form; with more rows the
+// tall form's rarer staging wins (CAS(20,20): 1.98 ms, flat 3.18).
+constexpr long kSlabTall = 131072, kSlabUnits = 8192;
+constexpr int kSlabFlatDepth = 16;  // k's of the flat form's strip
+
+void Solver::resolve_slab(Phase& ph, int slot, void* const* bases, size_t const* esz, const long* sizes) {
+  const auto tr0 = std::chrono::steady_clock::now();
+  for (const PSlabRun& r : ph.runs) {
+    DMRG_REQUIRE(r.boff >= 0 && r.K > 0 && r.boff + (long)(r.K - 1) * r.ldb + r.N <= sizes[B_PSI], ST_EINVAL,
+                 "plan: operand block out of bounds");
+    DMRG_REQUIRE((long)r.M * (r.j1 - r.j0) < (1L << 31) - (1 << 16), ST_EINVAL, "plan: too many stacked rows");
+    for (int j = r.j0; j < r.j1; ++j) {
+      const PSlabJob& jb = ph.jobs[j];
+      DMRG_REQUIRE(jb.aoff >= 0 && jb.aoff + (long)r.M * r.K <= sizes[jb.abuf], ST_EINVAL,
+                   "plan: operand block out of bounds");
+      DMRG_REQUIRE(jb.coff >= 0 && jb.coff + (long)(r.M - 1) * r.ldb + r.N <= sizes[B_T], ST_EINVAL,
+                   "plan: output block out of bounds");
+    }
+  }
+  if (stage_pending_) hip_check(hipEventSynchronize(stage_ev_), "staging");
+  SlabJob* jobs = stage_items_.get<SlabJob>((long)ph.jobs.size());
+  for (size_t j = 0; j < ph.jobs.size(); ++j) {
+    const PSlabJob& jb = ph.jobs[j];
+    jobs[j].X = (const char*)bases[jb.abuf] + jb.aoff * (long)esz[jb.abuf];
+    jobs[j].T = (char*)bases[B_T] + jb.coff * (long)esz[B_T];
+  }
+  auto n_strips = [](const PSlabRun& r) { return (r.N + 63) / 64; };
+  long rows = 0;  // stacked rows of all strips
+  for (const PSlabRun& r : ph.runs) rows += (long)r.M * (r.j1 - r.j0) * n_strips(r);
+  int kmax = 0;
+  for (const PSlabRun& r : ph.runs) kmax = std::max(kmax, r.K);
+  const bool tall = rows >= kSlabTall || kmax > kSlabFlatDepth;
+  ph.tall[slot] = tall;
+  const int per_unit = (int)std::min<long>(std::max<long>(256, (rows / kSlabUnits + 255) / 256 * 256), 4096);
+  long nun = 0;
+  for (const PSlabRun& r : ph.runs) {
+    const long s = (long)r.M * (r.j1 - r.j0), per = tall ? per_unit : 64;
+    nun += (s + per - 1) / per * n_strips(r);
+  }
+  // the strips of one row range go to one XCD (workgroups are dealt to the eight in
+  // turn): they read the same rows of X, and the lines of T where they meet are
+  // completed in its L2 (CAS(20,20): 2.4 -> 0.7 GB read, 1.93 -> 1.77 ms)
+  std::vector<SlabUnit> lists[8];
+  for (const PSlabRun& r : ph.runs) {
+    const long s = (long)r.M * (r.j1 - r.j0), per = tall ? per_unit : 64;
+    const int ns = n_strips(r), nb = (r.N + 15) / 16;
+    for (long r0 = 0; r0 < s; r0 += per) {
+      std::vector<SlabUnit>& l = *std::min_element(lists, lists + 8, [](const auto& x, const auto& y) { return x.size() < y.size(); });
+      for (int i = 0; i < ns; ++i) {
+        const int b0 = nb * i / ns, b1 = nb * (i + 1) / ns, n0 = 16 * b0, n = std::min(16 * b1, r.N) - n0;
+        l.push_back({(const char*)bases[B_PSI] + (r.boff + n0) * (long)esz[B_PSI], r.ldb, r.K, r.M, n, r.ldb, n0, r.j0,
+                     (int)r0, (int)std::min(s, r0 + per)});
+      }
+    }
+  }
+  SlabUnit* const units = stage_units_.get<SlabUnit>(nun);
+  SlabUnit* u = units;
+  for (size_t i = 0; u < units + nun; ++i)
+    for (const auto& l : lists)
+      if (i < l.size()) *u++ = l[i];
+  ph.n_units[slot] = (int)nun;
+  ph.d_items[slot].reserve(ph.jobs.size() * sizeof(SlabJob) + 64);
+  ph.d_units[slot].reserve(nun * sizeof(SlabUnit) + 64);
+  hip_check(hipMemcpyAsync(ph.d_items[slot].p, jobs, ph.jobs.size() * sizeof(SlabJob), hipMemcpyHostToDevice, st), "jobs");
+  hip_check(hipMemcpyAsync(ph.d_units[slot].p, units, nun * sizeof(SlabUnit), hipMemcpyHostToDevice, st), "units");
+  stage_sent();
+  for (int b = 0; b < B_NBUF; ++b) ph.last_bases[slot][b] = bases[b];
+  ph.uploaded[slot] = true;
+  st_.resolve_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - tr0).count();
+}
+
 void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* esz, const long* sizes) {
+  if (!ph.runs.empty()) {
+    const int sl = prec == PREC_F64 ? 0 : (prec == PREC_F32 ? 1 : 2);
+    bool same = ph.uploaded[sl];
+    for (int b = 0; b < B_NBUF && same; ++b) same = ph.last_bases[sl][b] == bases[b];
+    if (!same) resolve_slab(ph, sl, bases, esz, sizes);
+    launch_gemm_slab(prec, ph.tall[sl], ph.d_units[sl].as<SlabUnit>(), ph.n_units[sl], ph.d_items[sl].as<SlabJob>(), st);
+    return;
+  }
   if (ph.units.empty()) return;
   int slot = prec == PREC_F64 ? 0 : (prec == PREC_F32 ? 1 : 2);
   bool same = ph.uploaded[slot] && (ph.n_tiles[slot] == 0 || ph.slot_base[slot] == splitk_.p);
@@ -388,9 +478,8 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
   // fp64 / fp32 NT phases with long item lists (sigma phase B) take the stream
   // kernel: whole blocks up to 64 x 64 per wave, operands read once per block
   // (phase B at CAS(20,20), M = 1024: 7.5 ms with 64-row workgroup tiles, one
-  // item at a time; 4.9 ms here); bf16 and offsets past the reach take the
-  // one-wave kernels
-  const bool stream = ph.stream && (prec == PREC_F64 || prec == PREC_F32) && ph.mode == GEMM_NT && buf_ok;
+  // item at a time; 4.9 ms here); bf16 takes the one-wave kernel
+  const bool stream = ph.stream && (prec == PREC_F64 || prec == PREC_F32);
   ph.stream_used[slot] = stream;
   GemmUnit* units = nullptr;
   SplitTile* tiles = nullptr;
@@ -603,9 +692,7 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
   hip_check(hipMemcpyAsync(ph.d_units[slot].p, units, nun * sizeof(GemmUnit), hipMemcpyHostToDevice, st), "units");
   if (ntl > 0)
     hip_check(hipMemcpyAsync(ph.d_tiles[slot].p, tiles, ntl * sizeof(SplitTile), hipMemcpyHostToDevice, st), "tiles");
-  if (!stage_ev_) hip_check(hipEventCreateWithFlags(&stage_ev_, hipEventDisableTiming), "staging event");
-  hip_check(hipEventRecord(stage_ev_, st), "staging event");
-  stage_pending_ = true;
+  stage_sent();
   const auto tr2 = std::chrono::steady_clock::now();
   st_.resolve_ms += std::chrono::duration<double, std::milli>(tr2 - tr0).count();
   if (opt_.verbose > 1)
@@ -624,11 +711,8 @@ void Solver::launch_resolved(Phase& ph, int prec, int slot) {
                       ph.d_items[slot].as<GemmItem>(), st);
     if (ph.gemm_done) (void)hipEventRecord(ph.gemm_done, st);  // GEMM-only timing
     launch_splitk_reduce(ph.d_tiles[slot].as<SplitTile>(), ph.n_tiles[slot], splitk_.as<double>(), st);
-  } else if (prec == PREC_F32 && ph.stream_used[slot]) {
-    launch_gemm_stream(PREC_F32, 0, ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
-    launch_splitk_reduce_f32(ph.d_tiles[slot].as<SplitTile>(), ph.n_tiles[slot], splitk_.as<float>(), st);
   } else if (prec == PREC_F32) {
-    launch_gemm_w32_f32(ph.mode, ph.buf_ok[slot], ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
+    launch_gemm_stream(PREC_F32, 0, ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
     launch_splitk_reduce_f32(ph.d_tiles[slot].as<SplitTile>(), ph.n_tiles[slot], splitk_.as<float>(), st);
   } else if (prec == PREC_BF16 || prec == 3) {
     launch_gemm_w32_bf16(ph.mode, prec == 3, ph.buf_ok[slot], ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot],
@@ -1129,10 +1213,17 @@ void Solver::build_sigma_plan(int k) {
   });
   part.clear();
   const auto tp1 = clk::now();
-  // phase A: T_X = X psi over each run of consecutive column blocks that phase B reads
+  // phase A: T_X = X psi over each run of consecutive column blocks that phase B
+  // reads; the factors with one class, slab and run go into one list
+  struct SlabRunJobs {
+    PSlabRun run;
+    std::vector<PSlabJob> jobs;
+  };
+  std::vector<std::vector<SlabRunJobs>> runs(nch);
+  std::vector<std::map<std::array<int, 4>, int>> run_of(nch);  // (class, slab, first column, columns)
   for (size_t f = 0; f < lf_.fac.size(); ++f) {
     if (toff[f].empty()) continue;
-    Phase& pa = phA_[chunk_of[f]];
+    const int ch = chunk_of[f];
     const EnvClass& cls = envl.classes[lf_.fac[f].cls];
     for (size_t si = 0; si < P.slabs.size(); ++si) {
       if (toff[f][si] < 0) continue;
@@ -1147,15 +1238,22 @@ void Solver::build_sigma_plan(int k) {
         size_t b1 = b0 + 1;
         while (b1 < ub.size() && ub[b1] && sl.blocks[b1].col0 == sl.blocks[b1 - 1].col0 + sl.blocks[b1 - 1].mr) ++b1;
         const int c0 = sl.blocks[b0].col0, w = sl.blocks[b1 - 1].col0 + sl.blocks[b1 - 1].mr - c0;
-        int ib = (int)pa.items.size();
-        pa.items.push_back({lf_.fac[f].alias ? B_ENVL : B_XMIX, lf_.fac[f].off + eb.off, B_PSI, sl.off + c0,
-                            eb.mc, sl.width, eb.mc, 1.0});
-        add_units(pa.units, B_T, toff[f][si] + c0, sl.width, eb.mr, w, ib, ib + 1, 0);
-        pa.flops_exec += 2.0 * eb.mr * eb.mc * w;
+        const auto at = run_of[ch].try_emplace({lf_.fac[f].cls, (int)si, c0, w}, (int)runs[ch].size());
+        if (at.second) runs[ch].push_back({{sl.off + c0, sl.width, eb.mc, eb.mr, w, 0, 0}, {}});
+        runs[ch][at.first->second].jobs.push_back(
+            {lf_.fac[f].alias ? B_ENVL : B_XMIX, lf_.fac[f].off + eb.off, toff[f][si] + c0});
+        phA_[ch].flops_exec += 2.0 * eb.mr * eb.mc * w;
         b0 = b1;
       }
     }
   }
+  for (int c = 0; c < nch; ++c)
+    for (SlabRunJobs& r : runs[c]) {
+      r.run.j0 = (int)phA_[c].jobs.size();
+      phA_[c].jobs.insert(phA_[c].jobs.end(), r.jobs.begin(), r.jobs.end());
+      r.run.j1 = (int)phA_[c].jobs.size();
+      phA_[c].runs.push_back(r.run);
+    }
   const auto tp2 = clk::now();
   // phase B of chunk c adds into sigma; chunk 0 writes every output block (zero
   // where no item reaches it), later chunks only the blocks they have items for.
@@ -1283,7 +1381,7 @@ void Solver::build_sigma_plan(int k) {
     fprintf(stderr, "sigma plan k=%d (%d threads): items %.2f ms (generation %.2f), phase A %.2f ms, phase B %.2f ms\n",
             k, plan_threads(), ms(tp0, tp1), ms(tp0, tp05), ms(tp1, tp2), ms(tp2, clk::now()));
     // shape statistics: executed (tile-padded) vs useful flops per phase
-    for (const Phase* ph : {&phA_[0], &phB_[0]}) {
+    for (const Phase* ph : {&phB_[0]}) {
       double padded = 0, kpad = 0, ksum = 0;
       long nit = 0;
       for (const PUnit& u : ph->units)
@@ -1295,7 +1393,7 @@ void Solver::build_sigma_plan(int k) {
           ++nit;
         }
       fprintf(stderr, "plan k=%d phase %s: units %zu items %zu (unit-items %ld) useful %.3e padded %.3e (x%.1f) "
-              "mean K %.1f (padded %.1f)\n", k, ph == &phA_[0] ? "A" : "B", ph->units.size(), ph->items.size(), nit,
+              "mean K %.1f (padded %.1f)\n", k, "B", ph->units.size(), ph->items.size(), nit,
               ph->flops, padded, padded / std::max(ph->flops, 1.0), ksum / std::max(nit, 1L), kpad / std::max(nit, 1L));
     }
     {

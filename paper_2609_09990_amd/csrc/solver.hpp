@@ -158,6 +158,16 @@ struct PUnit {
   int ldc, M, N, m0, n0, ib, ie, acc;
 };
 
+// T_f = X_f psi of the factors jobs j0 .. j1 (all M x K) over psi's columns n0 .. n0 +
+// N of one slab (boff: its first element of column n0, row stride ldb).
+struct PSlabJob {
+  int abuf; long aoff, coff;  // coff: T_f's element of row 0, column n0
+};
+struct PSlabRun {
+  long boff;
+  int ldb, K, M, N, j0, j1;
+};
+
 // A relocatable grouped GEMM: one launch, pointers resolved per precision.
 struct Phase {
   int mode = GEMM_NN;
@@ -165,6 +175,8 @@ struct Phase {
   hipEvent_t gemm_done = nullptr;  // if set, recorded between the GEMM and the split-K reduction
   std::vector<PItem> items;
   std::vector<PUnit> units;
+  std::vector<PSlabJob> jobs;   // with runs (instead of items and units): T = X psi on the slab kernel
+  std::vector<PSlabRun> runs;
   double flops = 0.0;       // algorithmic flops (see build_sigma_plan for sigma)
   double flops_exec = -1;   // flops the launch executes, unpadded (-1: same as flops)
   // device copies per precision
@@ -178,6 +190,7 @@ struct Phase {
   bool stream = false;                     // long item lists: may take the stream kernel (NT)
   double split_work[2] = {0, 0};           // > 0: split-K granularity from this work (by cost unit), not the phase's own
   bool stream_used[3] = {false, false, false};
+  bool tall[3] = {false, false, false};    // slab phases: 256-row steps
 };
 
 // One side's factors for a middle cut: X_{beta,op} = sum_alpha c L[alpha] (left)
@@ -474,6 +487,8 @@ class Solver {
   void build_sigma_plan(int k);
   void build_diag_plan(int k);
   void run_phase(Phase& ph, int prec, void* const* bases, size_t const* esz, const long* sizes);
+  void resolve_slab(Phase& ph, int slot, void* const* bases, size_t const* esz, const long* sizes);
+  void stage_sent();
   void launch_resolved(Phase& ph, int prec, int slot);
   void ensure_lowp(int prec);
   void svd_step(int k, bool left_to_right, int nr, std::vector<DevMem>& next_guess, double& tau);
