@@ -32,7 +32,7 @@ enum GemmMode : int {
 };
 
 // Element precision of A and B (C is fp64 for FP64, fp32 otherwise).
-enum GemmPrec : int { PREC_F64 = 0, PREC_F32 = 1, PREC_BF16 = 2 };
+enum GemmPrec : int { PREC_F64 = 0, PREC_F32 = 1, PREC_BF16 = 2, PREC_BF16_A32 = 3 };
 
 void launch_gemm(int prec, int mode, const GemmUnit* units, int n_units, const GemmItem* items,
                  hipStream_t s);
@@ -105,7 +105,8 @@ struct SplitTile {
 };
 void launch_splitk_reduce(const SplitTile* tiles, int n, const double* slots, hipStream_t s);
 // NT stream kernel (gemm_stream.hip; prec PREC_F64 or PREC_F32: operands,
-// accumulation and outputs in that type): one wave per unit, tile (16 RB) x
+// accumulation and outputs in that type; PREC_BF16_A32: A fp32, rounded to bf16 after
+// the item's coefficient, B bf16, accumulation and outputs fp32): one wave per unit, tile (16 RB) x
 // (16 CB) with RB = shape >> 3 and CB = shape & 7 in 1..4.  The operands lie in
 // buffers with 64 readable bytes past their end (DevMem's slack); partial tiles
 // (accumulate == 2) are 16 CB wide.
@@ -127,11 +128,6 @@ struct SlabUnit {
 // otherwise 64 rows (four waves of 16) and 16 k's.
 void launch_gemm_slab(int prec, bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs, hipStream_t s);
 void launch_splitk_reduce_f32(const SplitTile* tiles, int n, const float* slots, hipStream_t s);
-// bf16 one-wave variant: A bf16 bits (a_f32 = false) or fp32 rounded to bf16,
-// B bf16 bits, fp32 accumulation and fp32 outputs / slots.
-void launch_gemm_w32_bf16(int mode, bool a_f32, bool buf, const GemmUnit* units, int n_units, const GemmItem* items,
-                          hipStream_t s);
-
 // out[f][j] = sum_{i in [ptr[f], ptr[f+1])} coef[i] * src[idx[i]][j], j < nnz.
 void launch_premix(double* out, const double* const* srcs, const int* ptr, const double* coef,
                    int n_out, long nnz, hipStream_t s);

@@ -475,17 +475,17 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
     }
   }, 4096);
   ph.buf_ok[slot] = buf_ok;
-  // fp64 / fp32 NT phases with long item lists (sigma phase B) take the stream
-  // kernel: whole blocks up to 64 x 64 per wave, operands read once per block
-  // (phase B at CAS(20,20), M = 1024: 7.5 ms with 64-row workgroup tiles, one
-  // item at a time; 4.9 ms here); bf16 takes the one-wave kernel
-  const bool stream = ph.stream && (prec == PREC_F64 || prec == PREC_F32);
-  ph.stream_used[slot] = stream;
+  // NT phases with long item lists (sigma phase B) take the stream kernel: whole
+  // blocks up to 64 x 64 per wave, operands read once per block (phase B at
+  // CAS(20,20), M = 1024: 7.5 ms with 64-row workgroup tiles, one item at a time;
+  // 5.3 ms here); the others (fp64 only) the one-wave kernel
+  const bool stream = ph.stream;
+  DMRG_REQUIRE(stream || prec == PREC_F64, ST_EINVAL, "plan: no low-precision form of this phase");
   GemmUnit* units = nullptr;
   SplitTile* tiles = nullptr;
   long nun = 0, ntl = 0;
   long n_slot_elems = 0;
-  if (prec == PREC_F64 || prec == PREC_F32 || prec == PREC_BF16 || prec == 3) {
+  {
     // One-wave tiles of (16 RB) x (16 CB), RB <= 4, CB <= 2: block rows are cut
     // into strips of 64 while more than 64 remain, columns into strips of 32, and
     // the last strip is rounded up to a multiple of 16 (MFMA blocks are 16 x 16).
@@ -545,8 +545,10 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
     // with one unit per block the longest chain of CAS(8,8), M = 60 took 150 us,
     // cut this way 10 us), and at most 5000 (CAS(20,20), M = 1024: 8.34 ms per
     // product with 16384 units of 9800, 8.12 with 32768, 8.76 with 65536).  fp32
-    // keeps its pieces (and with them its rounding) at 1/65536 of the work.
-    const double chunk = stream && !wide ? std::max(DMRG_SPLIT_MIN, work / 65536.0) : wide ? std::min(std::max(128.0, work / 16384.0), 5000.0) : std::max(DMRG_SPLIT_MIN, work / 16384.0);
+    // keeps its pieces (and with them its rounding) at 1/65536 of the work, bf16 at
+    // 1/16384.
+    const double chunk = wide ? std::min(std::max(128.0, work / 16384.0), 5000.0)
+                              : std::max(DMRG_SPLIT_MIN, work / (prec == PREC_F32 ? 65536.0 : 16384.0));
     // pass 1 (parallel over blocks): tiles and item chunks of each block, counts
     struct UnitPlan {
       std::vector<TileShape> ts;
@@ -671,16 +673,6 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
       }
     }, unit_grain(ph));
     ph.slot_base[slot] = splitk_.p;
-  } else {
-    std::vector<GemmUnit> v;
-    for (const PUnit& u : ph.units) {
-      char* C = (char*)bases[u.cbuf] + u.coff * esz[u.cbuf];
-      for (int m0 = 0; m0 < u.M; m0 += 64)
-        for (int n0 = 0; n0 < u.N; n0 += 64) v.push_back({C, u.ldc, u.M, u.N, m0, n0, u.ib, u.ie, u.acc});
-    }
-    nun = (long)v.size();
-    units = stage_units_.get<GemmUnit>(nun);
-    std::copy(v.begin(), v.end(), units);
   }
   ph.n_units[slot] = (int)nun;
   ph.n_tiles[slot] = (int)ntl;
@@ -703,23 +695,15 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
 }
 
 void Solver::launch_resolved(Phase& ph, int prec, int slot) {
+  const GemmUnit* units = ph.d_units[slot].as<GemmUnit>();
+  const GemmItem* items = ph.d_items[slot].as<GemmItem>();
+  if (ph.stream) launch_gemm_stream(prec, prec == PREC_F64 ? ph.tag : 0, units, ph.n_units[slot], items, st);
+  else launch_gemm_w32(ph.mode, ph.tag, ph.buf_ok[slot], units, ph.n_units[slot], items, st);
   if (prec == PREC_F64) {
-    if (ph.stream_used[slot])
-      launch_gemm_stream(PREC_F64, ph.tag, ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
-    else
-      launch_gemm_w32(ph.mode, ph.tag, ph.buf_ok[slot], ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot],
-                      ph.d_items[slot].as<GemmItem>(), st);
     if (ph.gemm_done) (void)hipEventRecord(ph.gemm_done, st);  // GEMM-only timing
     launch_splitk_reduce(ph.d_tiles[slot].as<SplitTile>(), ph.n_tiles[slot], splitk_.as<double>(), st);
-  } else if (prec == PREC_F32) {
-    launch_gemm_stream(PREC_F32, 0, ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
-    launch_splitk_reduce_f32(ph.d_tiles[slot].as<SplitTile>(), ph.n_tiles[slot], splitk_.as<float>(), st);
-  } else if (prec == PREC_BF16 || prec == 3) {
-    launch_gemm_w32_bf16(ph.mode, prec == 3, ph.buf_ok[slot], ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot],
-                         ph.d_items[slot].as<GemmItem>(), st);
-    launch_splitk_reduce_f32(ph.d_tiles[slot].as<SplitTile>(), ph.n_tiles[slot], splitk_.as<float>(), st);
   } else {
-    launch_gemm(prec, ph.mode, ph.d_units[slot].as<GemmUnit>(), ph.n_units[slot], ph.d_items[slot].as<GemmItem>(), st);
+    launch_splitk_reduce_f32(ph.d_tiles[slot].as<SplitTile>(), ph.n_tiles[slot], splitk_.as<float>(), st);
   }
 }
 

@@ -724,7 +724,7 @@ void Solver::sigma(int k, int prec, const double* psi, double* out) {
     if (prec == PREC_F32) launch_f64_to_f32(psi, lowp_[B_PSI].as<float>(), n, st);
     else launch_f64_to_bf16(psi, lowp_[B_PSI].as<uint16_t>(), n, st);
     pa_prec = prec == PREC_F32 ? PREC_F32 : PREC_BF16;
-    pb_prec = prec == PREC_F32 ? PREC_F32 : 3;
+    pb_prec = prec == PREC_F32 ? PREC_F32 : PREC_BF16_A32;
   }
   for (int c = 0; c < nch; ++c) {
     phA_[c].tag = 1 + 2 * kernel_tag_;

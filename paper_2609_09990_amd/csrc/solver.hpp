@@ -187,9 +187,8 @@ struct Phase {
   const void* last_bases[3][B_NBUF] = {};
   bool uploaded[3] = {false, false, false};
   bool buf_ok[3] = {false, false, false};  // every item fits the buffer-load kernels
-  bool stream = false;                     // long item lists: may take the stream kernel (NT)
+  bool stream = false;                     // long item lists: the stream kernel (NT)
   double split_work[2] = {0, 0};           // > 0: split-K granularity from this work (by cost unit), not the phase's own
-  bool stream_used[3] = {false, false, false};
   bool tall[3] = {false, false, false};    // slab phases: 256-row steps
 };
 
