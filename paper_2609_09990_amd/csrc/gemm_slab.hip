@@ -7,10 +7,9 @@
 // the rows of all the factors are stacked: a unit is a range of stacked rows times a
 // strip of at most 64 columns.
 //
-//  * The strip of psi is staged in LDS once per unit (64 k's, or 16; deeper ones
-//    go through in chunks), shared by the workgroup's waves; a wave's row tile
-//    (16 RB rows) may span any number of factors, so that rows are padded once per
-//    unit, not once per factor.
+//  * The strip of psi goes through LDS 16 k's at a time, shared by the workgroup's
+//    waves; a wave's row tile (16 RB rows) may span any number of factors, so that
+//    rows are padded once per unit, not once per factor.
 //  * Neighbouring lanes of a load or store take neighbouring bytes of a row: X goes
 //    through the wave's own LDS in windows of 128 bytes a row, and T leaves as
 //    column pairs, up to 256 bytes of a row from 16 lanes.  (X loaded in the MFMA
@@ -18,15 +17,16 @@
 //    2.7 times the write requests T needs, 2.5 ms.)  bf16 rows of X, 2-byte aligned,
 //    are loaded in the MFMA layout.
 //  * The next window is in flight while one is multiplied, across tiles; the next
-//    tile's matrices are looked up a tile ahead.  Eight waves of 32 rows rather than
-//    four of 64: the registers then let 16 waves share a CU.
+//    tile's matrices are looked up a tile ahead.  Little LDS (31 KB) and few
+//    registers, so that 16 or more waves share a CU: with the whole strip in LDS (64
+//    k's) and eight waves of 32 rows, 1.74 ms; four waves of 64 rows, 1.93 ms.
 //  * k order as in the one-wave kernels: fp64 / fp32 eight at a time (lane group
 //    kq holds 2 kq and 2 kq + 1), at most four left over as one step; bf16 sixteen
 //    at a time: fp32 and bf16 results keep their bits.
 //
-// Phase A at CAS(20,20), M = 1024: 2.8 -> 1.74 ms, of which writing the 4.5 GB of T
-// takes 0.75 and the MFMAs 0.75; CAS(12,12), M = 512: 420 -> 307 us; CAS(16,16),
-// M = 512, fp32: 388 -> 207 us, bf16: 376 -> 154 us.  (Storing a tile behind the next
+// Phase A at CAS(20,20), M = 1024: 2.8 -> 1.69 ms, of which writing the 4.5 GB of T
+// takes 0.75 and the MFMAs 0.75; CAS(12,12), M = 512: 420 -> 272 us; CAS(16,16),
+// M = 512, fp32: 388 -> 164 us, bf16: 376 -> 135 us.  (Storing a tile behind the next
 // one's first loads, so that no load waits for stores, spills: 1.94 ms.)
 #include <hip/hip_runtime.h>
 
@@ -43,12 +43,8 @@ typedef unsigned int v4ua __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned int v3ua __attribute__((ext_vector_type(3), aligned(4)));
 typedef unsigned int v2ua __attribute__((ext_vector_type(2), aligned(4)));
 
-// Two forms: tall (RB = 2), eight waves of 32 rows; flat (RB = 1), four of 16, for
-// phases with few rows and shallow blocks, whose units are to be resident all at once.
-// k's of the strip in LDS, waves of a workgroup, and k's of a window of X:
-constexpr int slab_depth(int rb) { return rb == 1 ? 16 : 64; }
-constexpr int slab_waves(int rb) { return rb == 1 ? 4 : 8; }
-constexpr int slab_window(int prec, int rb) { return rb == 2 && prec == PREC_F32 ? 32 : 16; }
+constexpr int KC = 16;  // k's of the strip in LDS, and of a window of X
+constexpr int NW = 4;   // waves of a workgroup, 16 RB rows each
 
 // KG: k's of one group; PITCH: row pitch of the strip, [k][column] (fp64, fp32: the
 // lane groups of one read fall on different banks) or [column][k] (bf16).  VW: elements
@@ -78,15 +74,15 @@ struct SlabElem<PREC_BF16> {
   typedef uint16_t in_t;
   typedef float out_t;
   typedef v4f acc_t;
-  static constexpr int KG = 16, PITCH = 68, VW = 0;
+  static constexpr int KG = 16, PITCH = KC + 4, VW = 0;
   __device__ static int row(int kq, int q) { return 4 * kq + q; }
 };
 
 template <int P, int RB>
 struct SlabLds {
   typedef SlabElem<P> E;
-  static constexpr int NW = slab_waves(RB), XP = slab_window(P, RB) + E::VW;  // XP: row pitch of a window
-  typename E::in_t b[(P == PREC_BF16 ? 64 : slab_depth(RB)) * E::PITCH];
+  static constexpr int XP = KC + E::VW;  // row pitch of a window
+  typename E::in_t b[(P == PREC_BF16 ? 64 : KC) * E::PITCH];
   typename E::in_t x[NW][P == PREC_BF16 ? 8 : 16 * RB * XP];
   const typename E::in_t* xrow[NW][16 * RB];  // per wave: rows of the tile being loaded
   typename E::out_t* trow[NW][2][16 * RB];    // and the output rows of a tile and the next one
@@ -106,7 +102,7 @@ __device__ inline void slab_tile(const SlabUnit& u, const SlabJob* __restrict__ 
   typedef typename E::out_t out_t;
   typedef typename E::acc_t acc_t;
   constexpr bool BF = P == PREC_BF16;
-  constexpr int KC = slab_depth(RB), NW = slab_waves(RB), KG = E::KG, PITCH = E::PITCH, KW = slab_window(P, RB), XP = SlabLds<P, RB>::XP;
+  constexpr int KG = E::KG, PITCH = E::PITCH, KW = KC, XP = SlabLds<P, RB>::XP;
   constexpr int LPR = BF ? 4 : KW / (E::VW > 0 ? E::VW : 1), RPI = 64 / LPR;  // lanes per row, rows per load
   constexpr int NL = BF ? RB * KW / KG : 16 * RB / RPI;                       // loads of a window
   const int r = lane & 15, kq = lane >> 4;
@@ -319,8 +315,8 @@ __device__ inline void slab_tile(const SlabUnit& u, const SlabJob* __restrict__ 
 }
 
 template <int P, int RB>
-__global__ __launch_bounds__(64 * slab_waves(RB), RB == 1 ? 5 : 4) void gemm_slab(const SlabUnit* __restrict__ units,
-                                                                                 const SlabJob* __restrict__ jobs) {
+__global__ __launch_bounds__(64 * NW, RB == 1 ? 5 : 4) void gemm_slab(const SlabUnit* __restrict__ units,
+                                                                     const SlabJob* __restrict__ jobs) {
   __shared__ __align__(16) SlabLds<P, RB> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const SlabUnit u = units[blockIdx.x];
@@ -334,8 +330,8 @@ __global__ __launch_bounds__(64 * slab_waves(RB), RB == 1 ? 5 : 4) void gemm_sla
 
 template <int P>
 void launch(bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs, hipStream_t s) {
-  if (tall) gemm_slab<P, 2><<<n_units, 64 * slab_waves(2), 0, s>>>(units, jobs);
-  else gemm_slab<P, 1><<<n_units, 64 * slab_waves(1), 0, s>>>(units, jobs);
+  if (tall) gemm_slab<P, 2><<<n_units, 64 * NW, 0, s>>>(units, jobs);
+  else gemm_slab<P, 1><<<n_units, 64 * NW, 0, s>>>(units, jobs);
 }
 
 }  // namespace

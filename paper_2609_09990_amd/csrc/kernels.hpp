@@ -124,8 +124,7 @@ struct SlabUnit {
   const void* B;
   int ldb, K, M, N, ldt, n0, job0, row0, row1;
 };
-// tall: 256 rows a step per workgroup (eight waves of 32), strips of 64 k's in LDS;
-// otherwise 64 rows (four waves of 16) and 16 k's.
+// tall: waves of 32 rows (128 rows a step per workgroup), otherwise of 16.
 void launch_gemm_slab(int prec, bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs, hipStream_t s);
 void launch_splitk_reduce_f32(const SplitTile* tiles, int n, const float* slots, hipStream_t s);
 // out[f][j] = sum_{i in [ptr[f], ptr[f+1])} coef[i] * src[idx[i]][j], j < nnz.

@@ -353,14 +353,12 @@ void Solver::stage_sent() {
 }
 
 // Slab phases: each run's stacked rows in strips of at most 64 columns and ranges of
-// rows, about kSlabUnits units and at least one step each (phase A at CAS(20,20),
-// M = 1024: 1.82 ms with 4096, 1.74 with 8192; CAS(12,12), M = 512: 307 and 310 us).
-// Short phases of shallow blocks (fewer than kSlabTall stacked rows, every K <= 16)
-// take the flat form, whose units hold 20 KB of LDS and are all resident: CAS(8,8),
-// M = 60, 105 thousand rows: 9.5 us, 13 to 15 in the tall form; with more rows the
-// tall form's rarer staging wins (CAS(20,20): 1.98 ms, flat 3.18).
-constexpr long kSlabTall = 131072, kSlabUnits = 8192;
-constexpr int kSlabFlatDepth = 16;  // k's of the flat form's strip
+// 256 rows (waves of 32 rows, two steps: phase A at CAS(20,20), M = 1024 1.69 ms,
+// 1.73 with one step, 1.69 with four; CAS(12,12), M = 512 272, 275 and 287 us).
+// Phases of fewer than kSlabTall stacked rows take ranges of 64 (waves of 16 rows, one
+// step), which fill the chip: CAS(8,8), M = 60, 22 thousand rows: 12.7 us with its
+// launch, 13.8 in ranges of 256; at 260 thousand rows both take 35 us.
+constexpr long kSlabTall = 131072;
 
 void Solver::resolve_slab(Phase& ph, int slot, void* const* bases, size_t const* esz, const long* sizes) {
   const auto tr0 = std::chrono::steady_clock::now();
@@ -386,14 +384,12 @@ void Solver::resolve_slab(Phase& ph, int slot, void* const* bases, size_t const*
   auto n_strips = [](const PSlabRun& r) { return (r.N + 63) / 64; };
   long rows = 0;  // stacked rows of all strips
   for (const PSlabRun& r : ph.runs) rows += (long)r.M * (r.j1 - r.j0) * n_strips(r);
-  int kmax = 0;
-  for (const PSlabRun& r : ph.runs) kmax = std::max(kmax, r.K);
-  const bool tall = rows >= kSlabTall || kmax > kSlabFlatDepth;
+  const bool tall = rows >= kSlabTall;
   ph.tall[slot] = tall;
-  const int per_unit = (int)std::min<long>(std::max<long>(256, (rows / kSlabUnits + 255) / 256 * 256), 4096);
+  const long per = tall ? 256 : 64;
   long nun = 0;
   for (const PSlabRun& r : ph.runs) {
-    const long s = (long)r.M * (r.j1 - r.j0), per = tall ? per_unit : 64;
+    const long s = (long)r.M * (r.j1 - r.j0);
     nun += (s + per - 1) / per * n_strips(r);
   }
   // the strips of one row range go to one XCD (workgroups are dealt to the eight in
@@ -401,7 +397,7 @@ void Solver::resolve_slab(Phase& ph, int slot, void* const* bases, size_t const*
   // completed in its L2 (CAS(20,20): 2.4 -> 0.7 GB read, 1.93 -> 1.77 ms)
   std::vector<SlabUnit> lists[8];
   for (const PSlabRun& r : ph.runs) {
-    const long s = (long)r.M * (r.j1 - r.j0), per = tall ? per_unit : 64;
+    const long s = (long)r.M * (r.j1 - r.j0);
     const int ns = n_strips(r), nb = (r.N + 15) / 16;
     for (long r0 = 0; r0 < s; r0 += per) {
       std::vector<SlabUnit>& l = *std::min_element(lists, lists + 8, [](const auto& x, const auto& y) { return x.size() < y.size(); });

@@ -189,7 +189,7 @@ struct Phase {
   bool buf_ok[3] = {false, false, false};  // every item fits the buffer-load kernels
   bool stream = false;                     // long item lists: the stream kernel (NT)
   double split_work[2] = {0, 0};           // > 0: split-K granularity from this work (by cost unit), not the phase's own
-  bool tall[3] = {false, false, false};    // slab phases: 256-row steps
+  bool tall[3] = {false, false, false};    // slab phases: waves of 32 rows
 };
 
 // One side's factors for a middle cut: X_{beta,op} = sum_alpha c L[alpha] (left)

@@ -1,6 +1,6 @@
 """GPU parity of the slab kernel (sigma phase A) where its units can go wrong: row ranges that
 span factors, strips of one and of more than 64 columns, blocks deeper than the strip in LDS
-(16 or 64), one-deep blocks, in every precision."""
+(16), one-deep blocks, in every precision."""
 import numpy as np
 import pytest
 
