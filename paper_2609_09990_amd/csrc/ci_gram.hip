@@ -12,9 +12,9 @@
 // whole A list with up to 128 B rows; a list of block pairs says which blocks are
 // wanted (a symmetric product takes half of them and gathers its rows once).
 // Bound by the gathers' instructions and the MFMAs together.  CAS(12,12) 1-/2-RDM:
-// 6.5 -> 0.75 ms per call (this kernel 0.57 ms, 32 TFLOP/s of wanted blocks; it was
+// 6.5 -> 0.64 ms per call (this kernel 0.57 ms, 32 TFLOP/s of wanted blocks; it was
 // two products of 0.94 ms, two passes of copies of 0.24 and 4 ms of host tables and
-// allocations); three-body density at CAS(10,10): 76 -> 2.9 ms (2.1 ms here; 9 ms of
+// allocations); three-body density at CAS(10,10): 76 -> 2.7 ms (2.1 ms here; 9 ms of
 // kernels before, the rest the allocation of 4 GB of copies).  Sorting the rows by
 // excitation instead of by source vector took 4.2 ms, 64-bit index arithmetic 4.0.
 //

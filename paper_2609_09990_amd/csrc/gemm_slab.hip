@@ -314,7 +314,9 @@ __device__ inline void slab_tile(const SlabUnit& u, const SlabJob* __restrict__ 
   }
 }
 
-template <int P, int RB>
+// TAG only gives each instantiation its own kernel name, so profiles can tell
+// launches apart.
+template <int P, int RB, int TAG>
 __global__ __launch_bounds__(64 * NW, RB == 1 ? 5 : 4) void gemm_slab(const SlabUnit* __restrict__ units,
                                                                      const SlabJob* __restrict__ jobs) {
   __shared__ __align__(16) SlabLds<P, RB> lds;
@@ -328,19 +330,21 @@ __global__ __launch_bounds__(64 * NW, RB == 1 ? 5 : 4) void gemm_slab(const Slab
   }
 }
 
-template <int P>
+template <int P, int TAG>
 void launch(bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs, hipStream_t s) {
-  if (tall) gemm_slab<P, 2><<<n_units, 64 * NW, 0, s>>>(units, jobs);
-  else gemm_slab<P, 1><<<n_units, 64 * NW, 0, s>>>(units, jobs);
+  if (tall) gemm_slab<P, 2, TAG><<<n_units, 64 * NW, 0, s>>>(units, jobs);
+  else gemm_slab<P, 1, TAG><<<n_units, 64 * NW, 0, s>>>(units, jobs);
 }
 
 }  // namespace
 
-void launch_gemm_slab(int prec, bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs, hipStream_t s) {
+void launch_gemm_slab(int prec, int tag, bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs,
+                      hipStream_t s) {
   if (n_units <= 0) return;
-  if (prec == PREC_F64) launch<PREC_F64>(tall, units, n_units, jobs, s);
-  else if (prec == PREC_F32) launch<PREC_F32>(tall, units, n_units, jobs, s);
-  else launch<PREC_BF16>(tall, units, n_units, jobs, s);
+  if (prec == PREC_F64 && tag == 3) launch<PREC_F64, 3>(tall, units, n_units, jobs, s);
+  else if (prec == PREC_F64) launch<PREC_F64, 1>(tall, units, n_units, jobs, s);
+  else if (prec == PREC_F32) launch<PREC_F32, 0>(tall, units, n_units, jobs, s);
+  else launch<PREC_BF16, 0>(tall, units, n_units, jobs, s);
 }
 
 }  // namespace dmrg

@@ -125,7 +125,8 @@ struct SlabUnit {
   int ldb, K, M, N, ldt, n0, job0, row0, row1;
 };
 // tall: waves of 32 rows (128 rows a step per workgroup), otherwise of 16.
-void launch_gemm_slab(int prec, bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs, hipStream_t s);
+void launch_gemm_slab(int prec, int tag, bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs,
+                      hipStream_t s);
 void launch_splitk_reduce_f32(const SplitTile* tiles, int n, const float* slots, hipStream_t s);
 // out[f][j] = sum_{i in [ptr[f], ptr[f+1])} coef[i] * src[idx[i]][j], j < nnz.
 void launch_premix(double* out, const double* const* srcs, const int* ptr, const double* coef,

@@ -430,7 +430,7 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
     bool same = ph.uploaded[sl];
     for (int b = 0; b < B_NBUF && same; ++b) same = ph.last_bases[sl][b] == bases[b];
     if (!same) resolve_slab(ph, sl, bases, esz, sizes);
-    launch_gemm_slab(prec, ph.tall[sl], ph.d_units[sl].as<SlabUnit>(), ph.n_units[sl], ph.d_items[sl].as<SlabJob>(), st);
+    launch_gemm_slab(prec, ph.tag, ph.tall[sl], ph.d_units[sl].as<SlabUnit>(), ph.n_units[sl], ph.d_items[sl].as<SlabJob>(), st);
     return;
   }
   if (ph.units.empty()) return;
