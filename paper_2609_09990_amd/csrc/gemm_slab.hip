@@ -96,7 +96,8 @@ __device__ inline void wave_fence() {
 
 // rows [row0, row1) of the unit's stacked rows times its strip of columns
 template <int P, int RB, int CB>
-__device__ inline void slab_tile(const SlabUnit& u, const SlabJob* __restrict__ jobs, int wave, int lane, SlabLds<P, RB>& lds) {
+__device__ inline void slab_tile(const SlabUnit& u, const SlabJob* __restrict__ jobs, int wave, int lane,
+                                 const typename SlabElem<P>::in_t* psi, SlabLds<P, RB>& lds) {
   typedef SlabElem<P> E;
   typedef typename E::in_t in_t;
   typedef typename E::out_t out_t;
@@ -121,7 +122,7 @@ __device__ inline void slab_tile(const SlabUnit& u, const SlabJob* __restrict__ 
   auto stage = [&](int k0) {
     const int n = min(lane, u.N - 1);
     const bool cv = lane < u.N;
-    const gin_t* B = (const gin_t*)u.B + n;
+    const gin_t* B = (const gin_t*)psi + u.boff + n;
     constexpr int ST = KC / NW;  // rows of each wave, all in flight
     in_t v[ST];
 #pragma unroll
@@ -318,33 +319,33 @@ __device__ inline void slab_tile(const SlabUnit& u, const SlabJob* __restrict__ 
 // launches apart.
 template <int P, int RB, int TAG>
 __global__ __launch_bounds__(64 * NW, RB == 1 ? 5 : 4) void gemm_slab(const SlabUnit* __restrict__ units,
-                                                                     const SlabJob* __restrict__ jobs) {
+                                                                     const SlabJob* __restrict__ jobs, const void* __restrict__ B) {
   __shared__ __align__(16) SlabLds<P, RB> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const SlabUnit u = units[blockIdx.x];
   switch ((u.N + 15) / 16) {
-    case 1: slab_tile<P, RB, 1>(u, jobs, wave, lane, lds); break;
-    case 2: slab_tile<P, RB, 2>(u, jobs, wave, lane, lds); break;
-    case 3: slab_tile<P, RB, 3>(u, jobs, wave, lane, lds); break;
-    default: slab_tile<P, RB, 4>(u, jobs, wave, lane, lds); break;
+    case 1: slab_tile<P, RB, 1>(u, jobs, wave, lane, (const typename SlabElem<P>::in_t*)B, lds); break;
+    case 2: slab_tile<P, RB, 2>(u, jobs, wave, lane, (const typename SlabElem<P>::in_t*)B, lds); break;
+    case 3: slab_tile<P, RB, 3>(u, jobs, wave, lane, (const typename SlabElem<P>::in_t*)B, lds); break;
+    default: slab_tile<P, RB, 4>(u, jobs, wave, lane, (const typename SlabElem<P>::in_t*)B, lds); break;
   }
 }
 
 template <int P, int TAG>
-void launch(bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs, hipStream_t s) {
-  if (tall) gemm_slab<P, 2, TAG><<<n_units, 64 * NW, 0, s>>>(units, jobs);
-  else gemm_slab<P, 1, TAG><<<n_units, 64 * NW, 0, s>>>(units, jobs);
+void launch(bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs, const void* B, hipStream_t s) {
+  if (tall) gemm_slab<P, 2, TAG><<<n_units, 64 * NW, 0, s>>>(units, jobs, B);
+  else gemm_slab<P, 1, TAG><<<n_units, 64 * NW, 0, s>>>(units, jobs, B);
 }
 
 }  // namespace
 
 void launch_gemm_slab(int prec, int tag, bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs,
-                      hipStream_t s) {
+                      const void* B, hipStream_t s) {
   if (n_units <= 0) return;
-  if (prec == PREC_F64 && tag == 3) launch<PREC_F64, 3>(tall, units, n_units, jobs, s);
-  else if (prec == PREC_F64) launch<PREC_F64, 1>(tall, units, n_units, jobs, s);
-  else if (prec == PREC_F32) launch<PREC_F32, 0>(tall, units, n_units, jobs, s);
-  else launch<PREC_BF16, 0>(tall, units, n_units, jobs, s);
+  if (prec == PREC_F64 && tag == 3) launch<PREC_F64, 3>(tall, units, n_units, jobs, B, s);
+  else if (prec == PREC_F64) launch<PREC_F64, 1>(tall, units, n_units, jobs, B, s);
+  else if (prec == PREC_F32) launch<PREC_F32, 0>(tall, units, n_units, jobs, B, s);
+  else launch<PREC_BF16, 0>(tall, units, n_units, jobs, B, s);
 }
 
 }  // namespace dmrg

@@ -114,19 +114,19 @@ void launch_gemm_stream(int prec, int tag, const GemmUnit* units, int n_units, c
 // Slab kernel (gemm_slab.hip): T_f = X_f B for the factors f of one block shape.  Job
 // job0 + f: X_f (M x K, row-major, row stride K) and T_f (row stride ldt; fp64 for
 // PREC_F64, fp32 otherwise).  A unit computes rows [row0, row1) of the factors' rows
-// stacked (row f M + m) and columns n0 .. n0 + N (at most 64): B points at column n0
-// of a K x .. row-major operand.  X is read up to 15 bytes past its last element.
+// stacked (row f M + m) and columns n0 .. n0 + N (at most 64): boff is the
+// element of B's row 0 and column n0 (row-major, row stride ldb).  X is read up to 15 bytes past its last element.
 struct SlabJob {
   const void* X;
   void* T;
 };
 struct SlabUnit {
-  const void* B;
+  long boff;
   int ldb, K, M, N, ldt, n0, job0, row0, row1;
 };
 // tall: waves of 32 rows (128 rows a step per workgroup), otherwise of 16.
 void launch_gemm_slab(int prec, int tag, bool tall, const SlabUnit* units, int n_units, const SlabJob* jobs,
-                      hipStream_t s);
+                      const void* B, hipStream_t s);
 void launch_splitk_reduce_f32(const SplitTile* tiles, int n, const float* slots, hipStream_t s);
 // out[f][j] = sum_{i in [ptr[f], ptr[f+1])} coef[i] * src[idx[i]][j], j < nnz.
 void launch_premix(double* out, const double* const* srcs, const int* ptr, const double* coef,

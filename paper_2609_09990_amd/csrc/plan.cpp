@@ -403,7 +403,7 @@ void Solver::resolve_slab(Phase& ph, int slot, void* const* bases, size_t const*
       std::vector<SlabUnit>& l = *std::min_element(lists, lists + 8, [](const auto& x, const auto& y) { return x.size() < y.size(); });
       for (int i = 0; i < ns; ++i) {
         const int b0 = nb * i / ns, b1 = nb * (i + 1) / ns, n0 = 16 * b0, n = std::min(16 * b1, r.N) - n0;
-        l.push_back({(const char*)bases[B_PSI] + (r.boff + n0) * (long)esz[B_PSI], r.ldb, r.K, r.M, n, r.ldb, n0, r.j0,
+        l.push_back({r.boff + n0, r.ldb, r.K, r.M, n, r.ldb, n0, r.j0,
                      (int)r0, (int)std::min(s, r0 + per)});
       }
     }
@@ -428,9 +428,9 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
   if (!ph.runs.empty()) {
     const int sl = prec == PREC_F64 ? 0 : (prec == PREC_F32 ? 1 : 2);
     bool same = ph.uploaded[sl];
-    for (int b = 0; b < B_NBUF && same; ++b) same = ph.last_bases[sl][b] == bases[b];
+    for (int b = 0; b < B_NBUF && same; ++b) same = b == B_PSI || ph.last_bases[sl][b] == bases[b];
     if (!same) resolve_slab(ph, sl, bases, esz, sizes);
-    launch_gemm_slab(prec, ph.tag, ph.tall[sl], ph.d_units[sl].as<SlabUnit>(), ph.n_units[sl], ph.d_items[sl].as<SlabJob>(), st);
+    launch_gemm_slab(prec, ph.tag, ph.tall[sl], ph.d_units[sl].as<SlabUnit>(), ph.n_units[sl], ph.d_items[sl].as<SlabJob>(), bases[B_PSI], st);
     return;
   }
   if (ph.units.empty()) return;

@@ -423,7 +423,7 @@ class Solver {
   std::vector<Phase> phA_, phB_;  // per chunk of left factors (build_sigma_plan)
   long t_size_ = 0;               // T_X doubles of the largest chunk
   std::vector<hipEvent_t> sig_ev_;  // phase boundaries of one sigma call (timing)
-  DevMem psi_in_, out_buf_, t_buf_;
+  DevMem out_buf_, t_buf_;
   // split-K partial tiles of whichever phase is running: phases run one after
   // another on the solver stream, so one scratch serves every cached plan
   DevMem splitk_;
