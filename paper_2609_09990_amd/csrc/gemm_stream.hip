@@ -25,7 +25,7 @@
 //    item's K are read (DevMem keeps 64 readable bytes past every buffer) and
 //    replaced by zeros in both operands.
 //
-// This phase at CAS(20,20), M = 1024: 7.5 -> 5.3 ms (18 GB of L2 misses; without the
+// This phase at CAS(20,20), M = 1024: 7.5 -> 5.3 ms (37 GB of L2 misses; without the
 // MFMAs 4.8 ms, with A from one place 2.8); CAS(12,12), M = 512: 1.36 -> 1.07 ms;
 // CAS(16,16), M = 512, with the bits of the kernels before: fp32 1.34 -> 0.84 ms,
 // bf16 0.94 -> 0.76 ms.  64-byte-wide windows (SL = 4) took 6.3 ms in fp64.

@@ -394,7 +394,7 @@ void Solver::resolve_slab(Phase& ph, int slot, void* const* bases, size_t const*
   }
   // the strips of one row range go to one XCD (workgroups are dealt to the eight in
   // turn): they read the same rows of X, and the lines of T where they meet are
-  // completed in its L2 (CAS(20,20): 2.4 -> 0.7 GB read, 1.93 -> 1.77 ms)
+  // completed in its L2 (CAS(20,20): 4.7 -> 1.4 GB read, 1.93 -> 1.77 ms)
   std::vector<SlabUnit> lists[8];
   for (const PSlabRun& r : ph.runs) {
     const long s = (long)r.M * (r.j1 - r.j0);
