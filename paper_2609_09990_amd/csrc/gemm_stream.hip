@@ -176,7 +176,7 @@ __device__ inline void stream_tile(const GemmUnit& u, const GemmItem* __restrict
 
   // depths of items kb + lane and kb + 64 + lane
   int kb = u.ib;
-  auto depth_of = [&](int i) { return items[min(i, u.ie - 1)].K; };
+  auto depth_of = [&](int i) { return list_depth(items, i, u.ib, u.ie); };
   int ka = depth_of(kb + lane), kc = depth_of(kb + 64 + lane);
   int it0 = u.ib, s0 = 0;  // next segment: segment s0 of item it0
 

@@ -25,6 +25,14 @@ struct GemmUnit {
   int shape;
 };
 
+// Depth of item i of a unit's list [ib, ie), the last one's past its end, for kernels
+// that look ahead.  0, and no read, where the list is empty: ib = ie may be 0, and
+// items[-1] lies in front of the table.
+__host__ __device__ inline int list_depth(const GemmItem* items, int i, int ib, int ie) {
+  if (ib >= ie) return 0;
+  return items[i < ie ? i : ie - 1].K;
+}
+
 enum GemmMode : int {
   GEMM_NN = 0,  // A: M x K row-major, B: K x N row-major
   GEMM_NT = 1,  // A: M x K row-major, B: N x K row-major (B transposed)

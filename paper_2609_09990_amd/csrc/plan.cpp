@@ -324,6 +324,7 @@ static bool validate_phase(const Phase& ph, const long* sizes, const size_t* esz
       const PUnit& u = ph.units[ui];
       long cmax = u.coff + (long)(u.M - 1) * u.ldc + (u.N - 1);
       if (u.coff < 0 || cmax >= sizes[u.cbuf]) bad[t] = 1;
+      if (u.ib < 0 || u.ie < u.ib || u.ie > (int)ph.items.size()) bad[t] = 3;
       for (int i = u.ib; i < u.ie && !bad[t]; ++i) {
         const PItem& it = ph.items[i];
         long amax, bmax;
@@ -340,6 +341,7 @@ static bool validate_phase(const Phase& ph, const long* sizes, const size_t* esz
   for (char b : bad) {
     if (b == 1) throw Error(ST_EINVAL, "plan: output block out of bounds");
     if (b == 2) throw Error(ST_EINVAL, "plan: operand block out of bounds");
+    if (b == 3) throw Error(ST_EINVAL, "plan: item list out of bounds");
   }
   bool ok = true;
   for (char r : reach) ok = ok && r;
