@@ -69,6 +69,7 @@ void MLP::get_params(float* host) const {
 void MLP::gemm(Tables& t, const void* A, const void* B, void* C, long rows, hipStream_t s) {
   if (t.key[0] != A || t.key[1] != B || t.key[2] != C || t.rows != rows) {
     hip_check(hipStreamSynchronize(s), "mlp tables");  // earlier uploads of the staging vectors are done
+    t.rows = -1;  // no tables until these are uploaded
     t.hu.clear();
     t.hi.clear();
     for (long m0 = 0; m0 < rows; m0 += 64) {

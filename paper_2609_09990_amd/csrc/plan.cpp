@@ -364,6 +364,7 @@ constexpr long kSlabTall = 131072;
 
 void Solver::resolve_slab(Phase& ph, int slot, void* const* bases, size_t const* esz, const long* sizes) {
   const auto tr0 = std::chrono::steady_clock::now();
+  ph.uploaded[slot] = false;  // until the tables are on the device
   for (const PSlabRun& r : ph.runs) {
     DMRG_REQUIRE(r.boff >= 0 && r.K > 0 && r.boff + (long)(r.K - 1) * r.ldb + r.N <= sizes[B_PSI], ST_EINVAL,
                  "plan: operand block out of bounds");
@@ -451,9 +452,8 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
     fprintf(stderr, "resolve: mode %d, %zu items, %s%s\n", ph.mode, ph.items.size(),
             ph.uploaded[slot] ? "moved buffers" : "first use", moved.c_str());
   }
+  ph.uploaded[slot] = false;  // until the tables are on the device: a failed allocation leaves none
   const bool buf_ok = validate_phase(ph, sizes, esz);
-  for (int b = 0; b < B_NBUF; ++b) ph.last_bases[slot][b] = bases[b];
-  ph.uploaded[slot] = true;
   // the tables are written into pinned staging buffers that every resolve of
   // the solver reuses (no page faults, DMA uploads); the last upload from them
   // must have finished (it precedes, in stream order, the kernels launched since)
@@ -683,6 +683,8 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
   if (ntl > 0)
     hip_check(hipMemcpyAsync(ph.d_tiles[slot].p, tiles, ntl * sizeof(SplitTile), hipMemcpyHostToDevice, st), "tiles");
   stage_sent();
+  for (int b = 0; b < B_NBUF; ++b) ph.last_bases[slot][b] = bases[b];
+  ph.uploaded[slot] = true;
   const auto tr2 = std::chrono::steady_clock::now();
   st_.resolve_ms += std::chrono::duration<double, std::milli>(tr2 - tr0).count();
   if (opt_.verbose > 1)

@@ -473,6 +473,7 @@ void Solver::prepare(int k) {
   ensure_right(k + 2);
   // park the current plan, then reuse the cached one of step k if its outer bonds match
   hip_check(hipStreamSynchronize(st), "prepare");  // host staging of the parked plan is no longer read
+  plan_k_ = -1;  // no step is ready until this one is: a failure below leaves none
   if (plan_built_k_ >= 0) {
     StepPlan& c = plan_cache_[plan_built_k_];
     c.key_l = bonds_at_build_l_;
@@ -580,6 +581,7 @@ double Solver::last_sigma_flops_exec() const {
 
 void Solver::ensure_lowp(int prec) {
   if (lowp_prec_ == prec) return;
+  lowp_prec_ = -1;  // the copies of another precision are overwritten from here on
   const int k = plan_k_;
   struct Src { int id; const double* p; long n; };
   Src src[] = {{B_ENVL, left_[k].buf.as<double>(), left_[k].size},

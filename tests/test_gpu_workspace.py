@@ -84,3 +84,45 @@ def test_workspace_query_covers_a_half_sweep_cas12():
     assert sol._ws.numel() == q  # no growth was needed
     assert st["workspace_peak_bytes"] <= q
     assert sol.workspace_query() >= 1.25 * st["workspace_peak_bytes"]
+
+
+def test_a_failed_allocation_leaves_nothing_that_counts_as_ready():
+    """Products after DMRG_ENOMEM in a workspace that is not grown, over steps, precisions and sizes:
+    each call either reports DMRG_ENOMEM again or writes the product, never an older one's."""
+    import ctypes as C
+    torch = _torch()
+    import paper_2609_09990_amd as pk
+    from paper_2609_09990_amd import _lib
+    n, M = 8, 100
+    h, B, e0 = synth.make_hamiltonian(n, 16, 0)
+    prob = pk.Problem(h, B, 4, 4, e0)
+    mps = synth.random_mps(n, 4, 4, M, seed=5)
+    ref = pk.Solver(prob, M=M, workspace=True)
+    ref.set_mps(mps["bonds"], mps["sites"])
+    calls = [(3, 0), (2, 2), (3, 1), (3, 0), (2, 0), (2, 1)]
+    x, want = {}, {}
+    for k, prec in set(calls):
+        x[k] = torch.from_numpy(synth.random_twosite(mps["bonds"], k, seed=12)).cuda()
+        want[k, prec] = torch.zeros_like(x[k])
+        ref.sigma(k, x[k], want[k, prec], prec)
+    full = ref.stats()["workspace_peak_bytes"]
+    seen = set()
+    for i in range(1, 25):
+        sol = pk.Solver(prob, M=M)
+        sol.set_mps(mps["bonds"], mps["sites"])
+        size = max(1 << 20, int(full * i / 20))
+        print(f"case {size} of {full:.0f} bytes", flush=True)
+        try:
+            sol.attach_workspace(size)
+        except pk.DMRGError as e:
+            assert e.code == -2
+            continue
+        for k, prec in calls + calls:
+            y, fl = torch.full_like(x[k], 7.0), C.c_double()
+            rc = _lib.dmrg_sigma(sol.h, k, prec, x[k].numel(), _lib._ptr(x[k]), _lib._ptr(y), C.byref(fl))
+            assert rc in (0, -2)
+            seen.add(rc)
+            if rc == 0:
+                tol = {0: 1e-13, 1: 1e-6, 2: 1e-2}[prec]  # two runs of one kernel; parts may differ in grouping
+                assert float((y - want[k, prec]).norm()) <= tol * float(want[k, prec].norm()), (i, k, prec)
+    assert seen == {0, -2}
