@@ -305,7 +305,11 @@ dmrg_status dmrg_s_squared(dmrg_solver* s, double* s2);
  * ascending orbital order, all alpha first; strings are ranked
  * colexicographically (rank = sum_t C(o_t, t+1) over sorted occupied orbitals);
  * a CI vector is the row-major matrix c[I_a][I_b], I_a < C(n, n_alpha),
- * I_b < C(n, n_beta).  Device memory is the caller's unless said otherwise; every call that takes
+ * I_b < C(n, n_beta).  Vectors and outputs are the caller's.  The calls' tables and
+ * scratch (dmrg_ci_rdm12, dmrg_ci_apply_v, dmrg_ci_rdm3, dmrg_rdm12 without a workspace)
+ * stay with the problem for the next call: at most two sets of at most 2 GiB of scratch each,
+ * given back when the problem is destroyed or when an allocation of this library does
+ * not fit beside them.  Every call that takes
  * device CI vectors takes their length n, which must be C(n_orb,n_alpha) C(n_orb,n_beta)
  * (DMRG_EINVAL otherwise). */
 /* String counts C(n_orb, n_alpha) and C(n_orb, n_beta).  Host only. */
@@ -398,7 +402,9 @@ dmrg_status dmrg_fiedler_order(int n, const double* I, int* order, double* fiedl
  * caller-owned): dE_dh[n_orb*n_orb], dE_dB[n_chol*n_orb*n_orb] (row-major like
  * the inputs; may be NULL when n_chol = 0), energies[n_states] (may be NULL):
  * <Psi_r|H|Psi_r>/<Psi_r|Psi_r> + e_core of every root (0 for roots without a
- * centre tensor).  Leaves the environments of root 0 in place. */
+ * centre tensor).  Leaves the environments of root 0 in place.  Without a workspace
+ * up to 1 GiB of the call's buffers stay with the solver for the next call, until
+ * it is destroyed or an allocation of this library does not fit beside them. */
 dmrg_status dmrg_grad(dmrg_solver* s, const double* state_weights, double* dE_dh, double* dE_dB,
                       double* energies);
 

@@ -306,6 +306,11 @@ void CiPool::give(std::unique_ptr<CiWork> w) {
   if (idle_.size() < 2) idle_.push_back(std::move(w));
 }
 
+void CiPool::drop() {
+  std::lock_guard<std::mutex> l(m_);
+  idle_.clear();
+}
+
 // V c with V = 1/2 sum_pqrs (pq|rs) E_pq E_rs and (pq|rs) = sum_Q B^Q_pq B^Q_rs,
 // streamed through the factors: T_rs = E_rs c, W_Q = sum_rs B^Q_rs T_rs,
 // U_pq = sum_Q B^Q_pq W_Q (one kernel, T and W on chip), V c = 1/2 sum_pq E_pq

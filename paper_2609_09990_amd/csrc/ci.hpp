@@ -98,7 +98,8 @@ void launch_rdm_assemble(const double* G, int ldg, int n, double scale, double* 
 // Device tables and scratch of the determinant-space calls of one problem.  A call
 // checks a set out, uses it alone and gives it back with its work done, so calls
 // from several threads and streams never share one; at most two idle sets are
-// kept, each up to kKeep bytes, until the problem is destroyed.
+// kept, each up to kKeep bytes, until the problem is destroyed or an allocation
+// fails.
 struct CiWork {
   int device = -1;
   bool tables = false;
@@ -106,11 +107,13 @@ struct CiWork {
   DevMem T1, T2, part, G, out, lists, F;
   std::vector<DevMem*> scratch() { return {&T1, &T2, &part, &G, &out, &lists, &F}; }
 };
-class CiPool {
+class CiPool : public IdleMemory {
  public:
+  ~CiPool() { retire(); }
   static constexpr size_t kKeep = size_t(2) << 30;
   std::unique_ptr<CiWork> take();
   void give(std::unique_ptr<CiWork> w);
+  void drop() override;
 
  private:
   std::mutex m_;

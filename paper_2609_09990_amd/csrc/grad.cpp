@@ -94,11 +94,38 @@ constexpr int kGSplit = 4096;
 
 }  // namespace
 
+size_t GradWork::bytes() const {
+  size_t n = P.bytes + Q.bytes + G.bytes;
+  for (const Tables& t : tab) n += t.tables.bytes + t.units.bytes + t.items.bytes;
+  for (int i = 0; i < 3; ++i) n += ph.d_items[i].bytes + ph.d_units[i].bytes + ph.d_tiles[i].bytes;
+  return n;
+}
+
+void GradWork::release() {
+  P.release();
+  Q.release();
+  G.release();
+  for (Tables& t : tab) t = Tables();
+  ph = Phase();
+}
+
+void GradWork::drop() {
+  std::lock_guard<std::mutex> l(m_);
+  if (users_ == 0 && !arena_) release();
+}
+
+void GradWork::enter(int d) {
+  std::lock_guard<std::mutex> l(m_);
+  users_ += d;
+  if (d > 0) arena_ = current_arena() != nullptr;
+}
+
 // g[e] = d<Psi|H|Psi>/dc_e for every entry of W_k (unnormalised state); with
 // norm != nullptr also <Psi|Psi> = sum_s < A_s R_{k+1}[H], L_k[I] A_s >_F (the
 // channels that are the identity on the left and on the right block).
 void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
   const MPO& mpo = prob_->mpo;
+  GradWork::Use use(grad_);
   ensure_left(k);
   ensure_right(k + 1);
   const Env& envl = left_[k];
@@ -250,7 +277,7 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
       gp.jobs.push_back(J);
     }
   };
-  auto run_rows = [&](bool left, GradPlan& gp, GradTables& t, double* out) {
+  auto run_rows = [&](bool left, GradPlan& gp, GradWork::Tables& t, double* out) {
     if (gp.units == 0) return;
     DMRG_REQUIRE(gp.units < (1L << 31), ST_EINVAL, "too many gradient products in one batch");
     gp.pack();
@@ -265,7 +292,7 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
   auto flush = [&]() {
     if (batch.empty()) return;
     // G = P Q^T, K cut into split-K items; the phase's device tables outlive the site
-    Phase& pg = grad_ph_;
+    Phase& pg = grad_.ph;
     pg.mode = GEMM_NT;
     pg.stream = true;
     pg.items.clear();
@@ -282,18 +309,18 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
       pg.units.push_back({B_XMIX, jb.goff, jb.nq, jb.np, jb.nq, 0, 0, ib, (int)pg.items.size(), 0});
       pg.flops += 2.0 * jb.np * jb.nq * (double)pc.K;
     }
-    grad_P_.reserve(std::max<long>(bp, 1) * 8);
-    grad_Q_.reserve(std::max<long>(bq, 1) * 8);
-    grad_G_.reserve(std::max<long>(bg, 1) * 8);
+    grad_.P.reserve(std::max<long>(bp, 1) * 8);
+    grad_.Q.reserve(std::max<long>(bq, 1) * 8);
+    grad_.G.reserve(std::max<long>(bg, 1) * 8);
     GradPlan pp, pq;
     make_rows(true, pp);
-    run_rows(true, pp, grad_tab_[0], grad_P_.as<double>());
+    run_rows(true, pp, grad_.tab[0], grad_.P.as<double>());
     make_rows(false, pq);
-    run_rows(false, pq, grad_tab_[1], grad_Q_.as<double>());
+    run_rows(false, pq, grad_.tab[1], grad_.Q.as<double>());
     void* bases[B_NBUF] = {};
-    bases[B_T] = grad_P_.p;
-    bases[B_OUT] = grad_Q_.p;
-    bases[B_XMIX] = grad_G_.p;
+    bases[B_T] = grad_.P.p;
+    bases[B_OUT] = grad_.Q.p;
+    bases[B_XMIX] = grad_.G.p;
     size_t esz[B_NBUF] = {8, 8, 8, 8, 8, 8, 8, 8, 8};
     long sizes[B_NBUF] = {};
     sizes[B_T] = bp;
@@ -301,7 +328,7 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
     sizes[B_XMIX] = bg;
     run_phase(pg, PREC_F64, bases, esz, sizes);
     Ghost.resize((size_t)bg);
-    hip_check(hipMemcpyAsync(Ghost.data(), grad_G_.p, Ghost.size() * 8, hipMemcpyDeviceToHost, st), "grad G");
+    hip_check(hipMemcpyAsync(Ghost.data(), grad_.G.p, Ghost.size() * 8, hipMemcpyDeviceToHost, st), "grad G");
     hip_check(hipStreamSynchronize(st), "grad site");  // the packed tables and staging die here
     for (const Job& jb : batch) {
       const int nQ = (int)classes[jb.c].qrow.size();
@@ -364,6 +391,7 @@ void Solver::grad(const std::vector<double>& w, std::vector<double>& dh, std::ve
   std::vector<double> dg;  // d E / d(pq|rs), entries independent
   if (nq > 0) dg.assign((size_t)n * n * n * n, 0.0);
   auto t0 = std::chrono::steady_clock::now();
+  GradWork::Use use(grad_);
 
   const int c = center_site_;
   auto invalidate_around = [&](int site) {
@@ -412,15 +440,7 @@ void Solver::grad(const std::vector<double>& w, std::vector<double>& dh, std::ve
     for (size_t ij = 0; ij < n2; ++ij) out[ij] += acc[ij];
   }
   // small buffers stay for the next call; a workspace gets everything back
-  size_t kept = grad_P_.bytes + grad_Q_.bytes + grad_G_.bytes;
-  for (const GradTables& t : grad_tab_) kept += t.tables.bytes + t.units.bytes + t.items.bytes;
-  if (current_arena() || kept > kKeepBytes) {
-    grad_P_.release();
-    grad_Q_.release();
-    grad_G_.release();
-    for (GradTables& t : grad_tab_) t = GradTables();
-    grad_ph_ = Phase();
-  }
+  if (current_arena() || grad_.bytes() > kKeepBytes) grad_.release();
   st_.grad_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
 }
 

@@ -10,7 +10,9 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <numeric>
+#include <set>
 
 namespace dmrg {
 
@@ -105,6 +107,33 @@ void* PinnedStage::reserve(size_t b) {
   return p;
 }
 
+namespace {
+struct IdleRegistry {
+  std::mutex m;
+  std::set<IdleMemory*> all;
+};
+IdleRegistry& idle_registry() {
+  static IdleRegistry* r = new IdleRegistry;  // outlives every object that leaves it at exit
+  return *r;
+}
+}  // namespace
+
+IdleMemory::IdleMemory() {
+  IdleRegistry& r = idle_registry();
+  std::lock_guard<std::mutex> l(r.m);
+  r.all.insert(this);
+}
+void IdleMemory::retire() {
+  IdleRegistry& r = idle_registry();
+  std::lock_guard<std::mutex> l(r.m);
+  r.all.erase(this);
+}
+void drop_idle_memory() {
+  IdleRegistry& r = idle_registry();
+  std::lock_guard<std::mutex> l(r.m);
+  for (IdleMemory* i : r.all) i->drop();
+}
+
 DevMem::~DevMem() { release(); }
 void DevMem::release() {
   if (p) {
@@ -135,6 +164,11 @@ void DevMem::reserve(size_t b) {
     return;
   }
   hipError_t e = hipMalloc(&p, b + kSlack);
+  if (e != hipSuccess) {
+    drop_idle_memory();
+    e = hipMalloc(&p, b + kSlack);
+    (void)hipGetLastError();  // reported here, not by the next call on this thread
+  }
   if (e != hipSuccess) {
     p = nullptr;
     throw Error(ST_ENOMEM, "device allocation of " + std::to_string(b) + " bytes failed");
@@ -1494,6 +1528,10 @@ void Solver::svd_step(int k, bool l2r, int nr, std::vector<DevMem>& next_guess, 
         }
       }
       rocblas_status rs = call();
+      if (rs == rocblas_status_memory_error) {
+        drop_idle_memory();
+        rs = call();
+      }
       if (rs != rocblas_status_success) throw Error(ST_EHIP, "rocsolver_dsyevd_strided_batched failed");
       info_off += (long)bk_.second.size();
       ++bi;

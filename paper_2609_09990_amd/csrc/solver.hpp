@@ -7,6 +7,7 @@
 
 #include <array>
 #include <map>
+#include <mutex>
 #include <memory>
 #include <vector>
 
@@ -112,6 +113,22 @@ struct DevMem {
   void release();
   template <class T> T* as() const { return (T*)p; }
 };
+
+// Device memory that an object keeps between its calls.  When an allocation fails,
+// everything idle is given back, from whichever thread needs it, and the allocation is
+// tried once more, so that what is kept never makes a call fail.
+class IdleMemory {
+ public:
+  IdleMemory(const IdleMemory&) = delete;
+  IdleMemory& operator=(const IdleMemory&) = delete;
+  virtual void drop() = 0;  // frees what no call is using; any thread
+
+ protected:
+  IdleMemory();
+  virtual ~IdleMemory() = default;
+  void retire();  // no drop() after this; first in the destructor of every derived class
+};
+void drop_idle_memory();
 
 void hip_check(hipError_t e, const char* what);
 bool same_sectors(const std::vector<Sector>& a, const std::vector<Sector>& b);
@@ -298,6 +315,36 @@ struct Deflated {
 struct MPSView {
   const std::vector<Bond>* bonds;
   const std::vector<SiteTensor>* sites;
+};
+
+// Buffers and tables of the integral gradient (grad.cpp), kept between calls.
+class GradWork : public IdleMemory {
+ public:
+  ~GradWork() { retire(); }
+  struct Tables {
+    DevMem tables, units, items;
+  };
+  DevMem P, Q, G;
+  Tables tab[2];  // P and Q rows of one batch of classes
+  Phase ph;       // their product
+  // A call that works on them: drop() from another thread leaves them alone, and
+  // always those of a workspace, whose memory only its solver's thread may free.
+  struct Use {
+    GradWork& w;
+    explicit Use(GradWork& x) : w(x) { w.enter(1); }
+    ~Use() { w.enter(-1); }
+    Use(const Use&) = delete;
+    Use& operator=(const Use&) = delete;
+  };
+  size_t bytes() const;
+  void release();
+  void drop() override;
+
+ private:
+  void enter(int d);
+  std::mutex m_;
+  int users_ = 0;
+  bool arena_ = false;
 };
 
 class Solver {
@@ -508,12 +555,7 @@ class Solver {
   void onesite_project(int k, double* x);
   void gemm_once(int mode, std::vector<GemmItem>& items, std::vector<GemmUnit>& units);
   void grad_site(int k, std::vector<double>& g, double* norm);
-  DevMem grad_P_, grad_Q_, grad_G_;
-  struct GradTables {
-    DevMem tables, units, items;
-  };
-  GradTables grad_tab_[2];  // P and Q rows of one batch of classes (grad.cpp)
-  Phase grad_ph_;           // their product
+  GradWork grad_;
 
   // learned preconditioner and training-triple store
   bool last_converged_ = true;
