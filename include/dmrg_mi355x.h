@@ -307,7 +307,7 @@ dmrg_status dmrg_s_squared(dmrg_solver* s, double* s2);
  * a CI vector is the row-major matrix c[I_a][I_b], I_a < C(n, n_alpha),
  * I_b < C(n, n_beta).  Vectors and outputs are the caller's.  The calls' tables and
  * scratch (dmrg_ci_rdm12, dmrg_ci_apply_v, dmrg_ci_rdm3, dmrg_rdm12 without a workspace)
- * stay with the problem for the next call: at most two sets of at most 2 GiB of scratch each,
+ * stay with the problem for the next call: at most two sets of at most 2.25 GiB of scratch each,
  * given back when the problem is destroyed or when an allocation of this library does
  * not fit beside them.  Every call that takes
  * device CI vectors takes their length n, which must be C(n_orb,n_alpha) C(n_orb,n_beta)

@@ -110,7 +110,9 @@ struct CiWork {
 class CiPool : public IdleMemory {
  public:
   ~CiPool() { retire(); }
-  static constexpr size_t kKeep = size_t(2) << 30;
+  // holds the largest three-body density: (6, 6) electrons in 12 orbitals, two vectors,
+  // 2.15e9 bytes (at 2 GiB every such call freed and allocated one set of copies)
+  static constexpr size_t kKeep = size_t(9) << 28;
   std::unique_ptr<CiWork> take();
   void give(std::unique_ptr<CiWork> w);
   void drop() override;

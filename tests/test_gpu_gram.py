@@ -62,3 +62,18 @@ def test_apply_v_edges(n, na, nb, nq):
     U = np.tensordot(F.T @ F, T, axes=1)
     ref = 0.5 * sum(space.apply_E(x // n, x % n, U[x]) for x in range(n * n))
     assert np.abs(got - ref).max() <= 1e-12 * max(np.abs(ref).max(), 1.0)
+
+
+# the largest call whose scratch is kept: a second one allocates nothing
+def test_largest_rdm3_keeps_its_scratch():
+    torch, prob, B, space, rng = _setup(12, 6, 6, 1)
+    import paper_2609_09990_amd as pk
+    h, B, e0 = synth.make_hamiltonian(4, 2, 2)
+    count = pk.Solver(pk.Problem(h, B, 2, 2, e0), M=4, workspace=True)  # for the library's allocation count
+    db, dk = (torch.from_numpy(rng.normal(size=space.shape)).cuda() for _ in range(2))
+    first = prob.ci_rdm3(db, dk)
+    n0 = count.stats()["device_allocs_since_attach"]
+    assert n0 > 0
+    second = prob.ci_rdm3(db, dk)
+    assert count.stats()["device_allocs_since_attach"] == n0
+    assert np.array_equal(first, second)
