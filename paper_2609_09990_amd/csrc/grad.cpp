@@ -85,8 +85,11 @@ int row_index(std::vector<std::pair<int, int>>& rows, std::vector<int>& idx, int
   return idx[at];
 }
 
-// Largest P or Q chunk, in doubles (two such buffers are live at once).
+// Largest P or Q chunk of one class, in doubles (two such buffers are live at once).
 constexpr long kChunkElems = 1L << 29;
+// Classes run together while their P and their Q rows stay below this many doubles
+// (CAS(16,16), M = 256: 54 ms with 2^26 and with 2^29, 59 with 2^24).
+constexpr long kBatchElems = 1L << 26;
 // P, Q and G buffers kept between calls, in bytes.
 constexpr size_t kKeepBytes = size_t(1) << 30;
 // K extent of one item of the G = P Q^T product (split-K granule).
@@ -126,8 +129,16 @@ void GradWork::enter(int d) {
 void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
   const MPO& mpo = prob_->mpo;
   GradWork::Use use(grad_);
-  ensure_left(k);
-  ensure_right(k + 1);
+  try {
+    ensure_left(k);
+    ensure_right(k + 1);
+  } catch (const Error& e) {  // again without the buffers of the site before
+    if (e.code != ST_ENOMEM || grad_.bytes() == 0) throw;
+    hip_check(hipStreamSynchronize(st), "grad site");
+    grad_.release();
+    ensure_left(k);
+    ensure_right(k + 1);
+  }
   const Env& envl = left_[k];
   const Env& envr = right_[k + 1];
   const Bond& bl = bonds_[k];
@@ -191,7 +202,8 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
   // Products of several classes run together (one launch each for all their P
   // rows, Q rows and G = P Q^T, one read-back): a site's classes are many and
   // small, and taken one at a time each cost three plans, six launches and a
-  // synchronisation (243 of them at CAS(12,12), M = 256).
+  // synchronisation (243 of them at CAS(12,12), M = 256).  Together they take
+  // at most kBatchElems or, beyond it, what the largest of them takes alone.
   // A class whose rows exceed the chunk bound runs by itself in chunks of rows.
   struct Job {
     size_t c;
@@ -340,34 +352,62 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
     batch.clear();
     bp = bq = bg = 0;
   };
-  for (size_t c = 0; c < classes.size(); ++c) {
-    const PairClass& pc = classes[c];
-    if (pc.prow.empty() || pc.K == 0) continue;
-    const int nP = (int)pc.prow.size(), nQ = (int)pc.qrow.size();
-    Gc[c].assign((size_t)nP * nQ, 0.0);
-    const int cP = (int)std::max<long>(1, std::min<long>(nP, kChunkElems / pc.K));
-    const int cQ = (int)std::max<long>(1, std::min<long>(nQ, kChunkElems / pc.K));
-    if (cP == nP && cQ == nQ) {
-      const long np = (long)nP * pc.K, nq = (long)nQ * pc.K;
-      if (bp + np > kChunkElems || bq + nq > kChunkElems) flush();
-      batch.push_back({c, 0, nP, 0, nQ, bp, bq, bg, true});
-      bp += np;
-      bq += nq;
-      bg += (long)nP * nQ;
-      continue;
+  // all products: classes batched up to `together` doubles of P or Q rows, the rows
+  // of a class that alone exceeds `alone` taken in chunks
+  auto run_all = [&](long together, long alone) {
+    batch.clear();
+    bp = bq = bg = 0;
+    for (size_t c = 0; c < classes.size(); ++c) {
+      const PairClass& pc = classes[c];
+      if (pc.prow.empty() || pc.K == 0) continue;
+      const int nP = (int)pc.prow.size(), nQ = (int)pc.qrow.size();
+      Gc[c].assign((size_t)nP * nQ, 0.0);
+      const int cP = (int)std::max<long>(1, std::min<long>(nP, alone / pc.K));
+      const int cQ = (int)std::max<long>(1, std::min<long>(nQ, alone / pc.K));
+      if (cP == nP && cQ == nQ) {
+        const long np = (long)nP * pc.K, nq = (long)nQ * pc.K;
+        if (bp + np > together || bq + nq > together) flush();
+        batch.push_back({c, 0, nP, 0, nQ, bp, bq, bg, true});
+        bp += np;
+        bq += nq;
+        bg += (long)nP * nQ;
+        continue;
+      }
+      flush();
+      for (int p0 = 0; p0 < nP; p0 += cP)
+        for (int q0 = 0; q0 < nQ; q0 += cQ) {
+          const int np = std::min(cP, nP - p0), nq = std::min(cQ, nQ - q0);
+          batch.push_back({c, p0, np, q0, nq, 0, 0, 0, q0 == 0});
+          bp = (long)np * pc.K;
+          bq = (long)nq * pc.K;
+          bg = (long)np * nq;
+          flush();
+        }
     }
     flush();
-    for (int p0 = 0; p0 < nP; p0 += cP)
-      for (int q0 = 0; q0 < nQ; q0 += cQ) {
-        const int np = std::min(cP, nP - p0), nq = std::min(cQ, nQ - q0);
-        batch.push_back({c, p0, np, q0, nq, 0, 0, 0, q0 == 0});
-        bp = (long)np * pc.K;
-        bq = (long)nq * pc.K;
-        bg = (long)np * nq;
-        flush();
-      }
+  };
+  // Where the buffers do not fit (a workspace, a full card), class by class, as
+  // little as the gradient ever took, and then half as many rows at a time down to one.
+  long largest = 0, deepest = 0;  // of one class: P or Q rows, one row
+  for (const PairClass& pc : classes) {
+    largest = std::max(largest, pc.K * (long)std::max(pc.prow.size(), pc.qrow.size()));
+    deepest = std::max(deepest, pc.K);
   }
-  flush();
+  long together = kBatchElems, alone = kChunkElems;
+  for (;;) {
+    const double flops0 = st_.grad_flops;
+    try {
+      run_all(together, alone);
+      break;
+    } catch (const Error& e) {
+      if (e.code != ST_ENOMEM || (together == 0 && alone <= deepest)) throw;
+      hip_check(hipStreamSynchronize(st), "grad site");
+      st_.grad_flops = flops0;
+      grad_.release();
+      if (together > 0) together = 0;
+      else alone = std::max(deepest, std::min(alone, largest) / 2);
+    }
+  }
   for (size_t e = 0; e < W.size(); ++e)
     for (const Use& u : uses[e]) g[e] += u.w * Gc[u.cls][(size_t)u.pr * (int)classes[u.cls].qrow.size() + u.qr];
   for (const Use& u : norm_uses) *norm += Gc[u.cls][(size_t)u.pr * (int)classes[u.cls].qrow.size() + u.qr];

@@ -28,3 +28,40 @@ def test_gradient_equals_densities(n, na, nb, nq, M):
         ref = np.einsum("pqrs,Qrs->Qpq", G, B)
         assert np.abs(dB - ref).max() <= 1e-11 * max(np.abs(ref).max(), 1.0)
         assert abs(e[0] - (np.sum(h * g) + 0.5 * np.sum(B * ref) + e0)) <= 1e-11 * max(1.0, abs(e[0]))
+
+
+def test_gradient_in_small_workspaces():
+    """In every workspace the gradient gives the same numbers, whether its classes run together, one by
+    one or in chunks of their rows, or it reports DMRG_ENOMEM."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_09990_amd as pk
+    n, na, nb, nq, M = 8, 4, 4, 12, 120
+    h, B, e0 = synth.make_hamiltonian(n, nq, 4)
+    prob = pk.Problem(h, B, na, nb, e0)
+    mps = synth.random_mps(n, na, nb, M, seed=3)
+
+    def solver(size):
+        s = pk.Solver(prob, M=M)
+        s.set_mps(mps["bonds"], mps["sites"])
+        s.attach_workspace(size)
+        return s
+
+    ref = solver(1 << 31)
+    want = ref.grad()
+    full = ref.stats()["workspace_peak_bytes"]
+    ran = 0
+    for pct in (105, 100, 90, 80, 75, 70, 60, 50, 40, 30, 20):
+        sol = solver(int(full * pct / 100) + 4096)
+        try:
+            got = sol.grad()
+        except pk.DMRGError as e:
+            assert e.code == -2
+            print(f"{pct}% of {full / 2**20:.0f} MiB: DMRG_ENOMEM", flush=True)
+            continue
+        ran += 1
+        diff = [float(np.abs(a - b).max() / max(np.abs(b).max(), 1.0)) for a, b in zip(got, want)]
+        print(f"{pct}% of {full / 2**20:.0f} MiB: {diff}", flush=True)
+        assert max(diff) <= 1e-11  # two fp64 orders of a few thousand unit-scale terms each
+    assert ran > 0
