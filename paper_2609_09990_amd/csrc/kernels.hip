@@ -19,6 +19,7 @@
 #include <stdexcept>
 
 #include "bf16.hpp"
+#include "jacobi.hpp"
 #include "kernels.hpp"
 
 namespace dmrg {
@@ -841,29 +842,18 @@ __device__ inline bool jacobi_significant(double apq, double app, double aqq) {
   return fabs(apq) > 1e-300 && fabs(apq) > 1e-15 * __builtin_amdgcn_sqrt(fabs(app * aqq));
 }
 // rotation of pair (p, q), p < q < k: c = 1, s = 0 when the coupling is not
-// significant.  t = tan of the angle from hardware estimates and one Newton step
-// (an inexact angle leaves a coupling of its relative error for the next sweep);
-// c = 1 / sqrt(1 + t^2) to full precision and s = t c, so the rotation is
-// orthogonal to rounding.  The exact divisions and roots, a chain of five, took
-// most of a round (125 us per call at k = 32).
+// significant
+struct HwEstimate {
+  __device__ static double rsq(double x) { return __builtin_amdgcn_rsq(x); }
+  __device__ static double rcp(double x) { return __builtin_amdgcn_rcp(x); }
+};
 __device__ inline void jacobi_angle(const double (*A)[65], int p, int q, double& c, double& s) {
   const double apq = A[p][q], app = A[p][p], aqq = A[q][q];
   const bool rot = jacobi_significant(apq, app, aqq);
-  double x = aqq - app, y = 2.0 * apq;
-  const double m = fmax(fabs(x), fabs(y));
-  const double sc = m < 0x1p-460 ? 0x1p500 : (m > 0x1p460 ? 0x1p-500 : 1.0);  // keeps h in range
-  x *= sc;
-  y *= sc;
-  const double h = fma(x, x, y * y);
-  const double g = __builtin_amdgcn_rsq(h), r0 = h * g, r = fma(0.5 * g, fma(-r0, r0, h), r0);
-  const double den = fabs(x) + r, i0 = __builtin_amdgcn_rcp(den), inv = i0 * fma(-den, i0, 2.0);
-  const double t = (x >= 0.0 ? y : -y) * inv, w = fma(t, t, 1.0);
-  double cc = __builtin_amdgcn_rsq(w);
-  cc *= fma(-0.5 * w * cc, cc, 1.5);
-  cc *= fma(-0.5 * w * cc, cc, 1.5);
-  cc = fma(0.5 * cc, fma(-w * cc, cc, 1.0), cc);
+  double cc, ss;
+  jacobi_rotation<HwEstimate>(app, aqq, apq, cc, ss);
   c = rot ? cc : 1.0;
-  s = rot ? t * cc : 0.0;
+  s = rot ? ss : 0.0;
 }
 
 __global__ __launch_bounds__(256) void jacobi_eig_kernel(const double* __restrict__ G, int ldg, int k,
