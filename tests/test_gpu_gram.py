@@ -77,3 +77,45 @@ def test_largest_rdm3_keeps_its_scratch():
     second = prob.ci_rdm3(db, dk)
     assert count.stats()["device_allocs_since_attach"] == n0
     assert np.array_equal(first, second)
+
+
+# the product instance of 11 and 12 orbitals (up to 272 rows): three-body densities sampled, and a
+# transition 1-/2-RDM; tolerances as above
+@pytest.mark.parametrize("n,na,nb,same", [(11, 2, 2, False), (11, 1, 2, True), (12, 2, 1, False)])
+def test_rdm3_of_eleven_and_twelve_orbitals(n, na, nb, same):
+    torch, prob, B, space, rng = _setup(n, na, nb, 1)
+    bra = rng.normal(size=space.shape)
+    ket = bra if same else rng.normal(size=space.shape)
+    db = torch.from_numpy(bra).cuda()
+    G = prob.ci_rdm3(db, db if same else torch.from_numpy(ket).cuda())
+    for _ in range(60):
+        p, q, r, s, t, u = (int(x) for x in rng.integers(0, n, size=6))
+        ref = np.sum(space.apply_E(q, p, bra) * space.apply_E(r, s, space.apply_E(t, u, ket)))
+        assert abs(G[p, q, r, s, t, u] - ref) <= 1e-12 * max(np.abs(G).max(), 1.0)
+
+
+@pytest.mark.parametrize("n,na,nb", [(11, 3, 2), (12, 2, 3), (14, 2, 2)])
+def test_transition_rdm12_of_many_orbitals(n, na, nb):
+    torch, prob, B, space, rng = _setup(n, na, nb, 1)
+    bra, ket = rng.normal(size=space.shape), rng.normal(size=space.shape)
+    g, G, ov = prob.ci_rdm12(torch.from_numpy(bra).cuda(), torch.from_numpy(ket).cuda())
+    rg, rG = fci.trdm12(space, bra, ket)
+    scale = max(np.abs(rG).max(), 1.0)
+    assert np.abs(g - rg).max() <= 1e-12 * scale
+    assert np.abs(G - rG).max() <= 1e-12 * scale
+    assert abs(ov - np.sum(bra * ket)) <= 1e-12 * scale
+
+
+# more determinants than the grid's 512 workgroups of 32: the loop over slices and the gather of the
+# next one, in both row-block instances, with one and with two passes of factors
+@pytest.mark.parametrize("n,na,nb,nq", [(12, 3, 3, 40), (13, 3, 2, 70), (16, 2, 3, 5)])
+def test_apply_v_many_slices(n, na, nb, nq):
+    torch, prob, B, space, rng = _setup(n, na, nb, nq)
+    assert space.size > 512 * 32
+    c = rng.normal(size=space.shape)
+    got = prob.ci_apply_v(torch.from_numpy(c).cuda()).cpu().numpy()
+    T = np.stack([space.apply_E(r, s, c) for r in range(n) for s in range(n)])
+    F = B.reshape(nq, n * n)
+    U = np.tensordot(F.T @ F, T, axes=1)
+    ref = 0.5 * sum(space.apply_E(x // n, x % n, U[x]) for x in range(n * n))
+    assert np.abs(got - ref).max() <= 1e-12 * max(np.abs(ref).max(), 1.0)
