@@ -541,12 +541,16 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
     // One-wave kernels: about 16384 units.  Stream kernel, fp64: as many, but
     // at least 128 block steps each (a unit's start costs about as much as 100:
     // with one unit per block the longest chain of CAS(8,8), M = 60 took 150 us,
-    // cut this way 10 us), and at most 5000 (CAS(20,20), M = 1024: 8.34 ms per
-    // product with 16384 units of 9800, 8.12 with 32768, 8.76 with 65536).  fp32
-    // keeps its pieces (and with them its rounding) at 1/65536 of the work, bf16 at
-    // 1/16384.
-    const double chunk = wide ? std::min(std::max(128.0, work / 16384.0), 5000.0)
-                              : std::max(DMRG_SPLIT_MIN, work / (prec == PREC_F32 ? 65536.0 : 16384.0));
+    // cut this way 10 us), and at most 3500 up to 131072 units.  A product at
+    // CAS(20,20), M = 1024 with units of up to 5000, 3500 and 2000 block steps:
+    // 7.09, 6.99 and 6.97 ms on a random state (mean K 12); 7.49, 7.35 and 7.27 on
+    // the state of a half sweep (mean K 23; this kernel alone 5.55, 5.37 and 5.19,
+    // one workgroup of up to 96 rows per block took 5.46), with 0.37, 0.53 and 0.89
+    // GB of partial tiles.  CAS(24,24), M = 2048, random: 43.6 ms with 5000 (3 GB),
+    // 42.4 with 2000 (7 GB), 46.6 with 20000.  fp32 keeps its pieces (and with
+    // them its rounding) at 1/65536 of the work, bf16 at 1/16384.
+    double chunk = wide ? std::min(std::max(128.0, work / 16384.0), std::max(3500.0, work / 131072.0))
+                        : std::max(DMRG_SPLIT_MIN, work / (prec == PREC_F32 ? 65536.0 : 16384.0));
     // pass 1 (parallel over blocks): tiles and item chunks of each block, counts
     struct UnitPlan {
       std::vector<TileShape> ts;
