@@ -438,7 +438,8 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
   }
   if (ph.units.empty()) return;
   int slot = prec == PREC_F64 ? 0 : (prec == PREC_F32 ? 1 : 2);
-  bool same = ph.uploaded[slot] && (ph.n_tiles[slot] == 0 || ph.slot_base[slot] == splitk_.p);
+  bool same = ph.uploaded[slot] &&
+              (ph.n_tiles[slot] == 0 || (ph.slot_base[slot] == splitk_.p && ph.slot_bytes[slot] <= splitk_.bytes));
   for (int b = 0; b < B_NBUF && same; ++b) same = ph.last_bases[slot][b] == bases[b];
   if (same) {  // plan already resolved against these buffers
     launch_resolved(ph, prec, slot);
@@ -557,53 +558,66 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
       std::vector<std::pair<int, int>> cuts;  // empty: no split
       long n_units = 0, n_tiles = 0, n_slot = 0;
     };
-    std::vector<UnitPlan> up(nu);
-    std::vector<char> too_big(plan_threads(), 0);
-    parallel_ranges(nu, [&](int t, long u0, long u1) {
-      for (long x = u0; x < u1; ++x) {
-        const PUnit& u = ph.units[x];
-        UnitPlan& q = up[x];
-        tiles_of(u, q.ts);
-        const double kchunk = chunk / (double)tile_step_cost(u, wide);  // 4-deep k steps per unit
-        long w = 0;
-        for (int i = u.ib; i < u.ie; ++i) w += (ph.items[i].K + 3) / 4;
-        if ((double)w <= kchunk || u.ie - u.ib <= 1) {
-          q.n_units = (long)q.ts.size();
-          continue;
-        }
-        // the same item chunks for every tile of the block; units chunk-major, so the
-        // waves of one workgroup run one chunk on neighbouring tiles (shared rows of A
-        // or columns of B)
-        for (int b = u.ib; b < u.ie;) {
-          int e = b;
-          double cw = 0;
-          while (e < u.ie && (cw < kchunk || e == b)) cw += (ph.items[e++].K + 3) / 4;
-          q.cuts.push_back({b, e});
-          b = e;
-        }
-        const long nc = (long)q.cuts.size();
-        q.n_units = nc * (long)q.ts.size();
-        q.n_tiles = (long)q.ts.size();
-        for (const TileShape& ts : q.ts) {
-          // the reduction covers tiles of up to 64 x 64 elements
-          if (ts.tm * ts.tn > 64 * 64) too_big[t] = 1;
-          q.n_slot += nc * ts.tm * ts.tn;
-        }
-      }
-    }, unit_grain(ph));
-    for (char b : too_big) DMRG_REQUIRE(!b, ST_EINVAL, "split-K tile larger than the reduction covers");
-    // offsets, then pass 2 (parallel): units, tiles and slot offsets in place
+    std::vector<UnitPlan> up;
     std::vector<long> uat(nu), tat(nu), sat(nu), cat(nu);
     long ncut = 0;  // (block, chunk) pairs
-    for (long x = 0; x < nu; ++x) {
-      uat[x] = nun;
-      tat[x] = ntl;
-      sat[x] = n_slot_elems;
-      cat[x] = ncut;
-      nun += up[x].n_units;
-      ntl += up[x].n_tiles;
-      n_slot_elems += up[x].n_slot;
-      ncut += std::max<long>(1, (long)up[x].cuts.size());
+    const size_t slot_esz = prec == PREC_F64 ? sizeof(double) : sizeof(float);
+    for (;; chunk *= 4) {
+      up.assign(nu, {});
+      std::vector<char> too_big(plan_threads(), 0);
+      parallel_ranges(nu, [&](int t, long u0, long u1) {
+        for (long x = u0; x < u1; ++x) {
+          const PUnit& u = ph.units[x];
+          UnitPlan& q = up[x];
+          tiles_of(u, q.ts);
+          const double kchunk = chunk / (double)tile_step_cost(u, wide);  // 4-deep k steps per unit
+          long w = 0;
+          for (int i = u.ib; i < u.ie; ++i) w += (ph.items[i].K + 3) / 4;
+          if ((double)w <= kchunk || u.ie - u.ib <= 1) {
+            q.n_units = (long)q.ts.size();
+            continue;
+          }
+          // the same item chunks for every tile of the block; units chunk-major, so the
+          // waves of one workgroup run one chunk on neighbouring tiles (shared rows of A
+          // or columns of B)
+          for (int b = u.ib; b < u.ie;) {
+            int e = b;
+            double cw = 0;
+            while (e < u.ie && (cw < kchunk || e == b)) cw += (ph.items[e++].K + 3) / 4;
+            q.cuts.push_back({b, e});
+            b = e;
+          }
+          const long nc = (long)q.cuts.size();
+          q.n_units = nc * (long)q.ts.size();
+          q.n_tiles = (long)q.ts.size();
+          for (const TileShape& ts : q.ts) {
+            // the reduction covers tiles of up to 64 x 64 elements
+            if (ts.tm * ts.tn > 64 * 64) too_big[t] = 1;
+            q.n_slot += nc * ts.tm * ts.tn;
+          }
+        }
+      }, unit_grain(ph));
+      for (char b : too_big) DMRG_REQUIRE(!b, ST_EINVAL, "split-K tile larger than the reduction covers");
+      // offsets
+      nun = ntl = n_slot_elems = ncut = 0;
+      for (long x = 0; x < nu; ++x) {
+        uat[x] = nun;
+        tat[x] = ntl;
+        sat[x] = n_slot_elems;
+        cat[x] = ncut;
+        nun += up[x].n_units;
+        ntl += up[x].n_tiles;
+        n_slot_elems += up[x].n_slot;
+        ncut += std::max<long>(1, (long)up[x].cuts.size());
+      }
+      if (n_slot_elems == 0) break;
+      // a move invalidates other resolved plans, which re-resolve (slot_base, slot_bytes)
+      try {
+        splitk_.reserve(n_slot_elems * slot_esz);
+        break;
+      } catch (const Error& e) {  // no room for the partial tiles: larger chunks need fewer
+        if (e.code != ST_ENOMEM) throw;
+      }
     }
     // Stream units run in the order of the operand their chunk starts at (the T_X
     // offset: factor by factor), not block by block: blocks that read the same
@@ -639,9 +653,7 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
     }
     units = stage_units_.get<GemmUnit>(nun);
     tiles = stage_tiles_.get<SplitTile>(ntl);
-    // grow-only: a move invalidates other resolved plans, which re-resolve (slot_base)
-    const size_t slot_esz = prec == PREC_F64 ? sizeof(double) : sizeof(float);
-    if (n_slot_elems > 0) splitk_.reserve(n_slot_elems * slot_esz);
+    // pass 2 (parallel): units, tiles and slot offsets in place
     char* const slot0 = (char*)splitk_.p;
     parallel_ranges(nu, [&](int, long u0, long u1) {
       for (long x = u0; x < u1; ++x) {
@@ -675,6 +687,7 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
       }
     }, unit_grain(ph));
     ph.slot_base[slot] = splitk_.p;
+    ph.slot_bytes[slot] = n_slot_elems * slot_esz;
   }
   ph.n_units[slot] = (int)nun;
   ph.n_tiles[slot] = (int)ntl;

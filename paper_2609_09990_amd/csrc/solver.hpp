@@ -200,6 +200,7 @@ struct Phase {
   DevMem d_items[3], d_units[3];
   DevMem d_tiles[3];                 // split-K tile table per precision slot
   const void* slot_base[3] = {};     // split-K scratch the units were resolved against
+  size_t slot_bytes[3] = {0, 0, 0};  // and how much of it they use
   int n_units[3] = {0, 0, 0}, n_tiles[3] = {0, 0, 0};
   const void* last_bases[3][B_NBUF] = {};
   bool uploaded[3] = {false, false, false};

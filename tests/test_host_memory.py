@@ -1,4 +1,4 @@
-"""CPU test of the memory that the integral gradient takes.  The program runs the library's host code
+"""CPU tests of the memory that the integral gradient and a product take.  The program runs the library's host code
 on a HIP runtime of its own: device memory is host memory with a budget, and kernels do nothing, so
 that the state's norm is zero and a gradient that came through every site ends in DMRG_ESTATE."""
 import os
@@ -49,6 +49,7 @@ hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)1
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* t, hipEvent_t, hipEvent_t) { *t = 1.f; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
@@ -60,7 +61,41 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* l, hipStream_t* s
   return hipSuccess;
 }
 }
-int main() {
+// least budget of prepare + product, the peak before the product and the peak without a budget
+int sigma_memory(dmrg_problem* p, dmrg_options o, int k) {
+  size_t before = 0;
+  auto run = [&](size_t budget) {
+    dmrg_solver* s = nullptr;
+    if (dmrg_solver_create(p, &o, nullptr, &s) != DMRG_OK) std::exit(1);
+    g_budget = budget;
+    g_peak = 0;
+    int64_t len = 0;
+    double fl;
+    dmrg_status rc = dmrg_prepare(s, k, &len);
+    before = g_peak;
+    if (rc == DMRG_OK) {
+      std::vector<double> psi(len), out(len);
+      for (int twice = 0; twice < 2 && rc == DMRG_OK; ++twice)
+        rc = dmrg_sigma(s, k, 0, len, psi.data(), out.data(), &fl);
+    }
+    g_budget = size_t(1) << 60;
+    dmrg_solver_destroy(s);
+    return rc;
+  };
+  if (run(size_t(1) << 60) != DMRG_OK) return 2;
+  const size_t full = g_peak, prepared = before;
+  size_t lo = prepared / 2, hi = full;
+  while (hi - lo > full / 256) {
+    const size_t mid = lo + (hi - lo) / 2;
+    const dmrg_status rc = run(mid);
+    if (rc != DMRG_OK && rc != DMRG_ENOMEM) return 3;
+    if (rc == DMRG_OK) hi = mid;
+    else lo = mid;
+  }
+  std::printf("%zu %zu %zu\n", prepared, hi, full);
+  return 0;
+}
+int main(int argc, char**) {
   const int n = 10, nq = 8, M = 200;
   std::vector<double> h(n * n), B(nq * n * n), dh(n * n), dB(nq * n * n);
   for (int i = 0; i < n; ++i)
@@ -72,6 +107,7 @@ int main() {
   dmrg_options_default(&o);
   o.M = M;
   if (dmrg_problem_create(n, 5, 5, nq, h.data(), B.data(), 0.0, &p) != DMRG_OK) return 1;
+  if (argc > 1) return sigma_memory(p, o, n / 2 - 1);
   // status of a gradient within a budget; held: what stays beside the gradient's own buffers
   size_t held = 0;
   auto run = [&](size_t budget) {
@@ -103,7 +139,7 @@ int main() {
 """
 
 
-def test_gradient_runs_in_less_memory_than_its_largest_batch(tmp_path):
+def _program(tmp_path):
     import paper_2609_09990_amd as pk
     assert os.path.dirname(pk.LIB_PATH) == PKG
     src, exe = tmp_path / "grad.cpp", tmp_path / "grad"
@@ -112,9 +148,23 @@ def test_gradient_runs_in_less_memory_than_its_largest_batch(tmp_path):
                     "-I" + os.path.join(PKG, "csrc"), "-I" + os.path.join(ROOT, "include"), str(src), "-o", str(exe),
                     "-L" + PKG, "-l:libdmrg_mi355x.so", "-Wl,-rpath," + PKG, "-Wl,-rpath,/opt/rocm/lib",
                     "-Wl,--allow-shlib-undefined", "-rdynamic"], check=True)
-    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    return str(exe)
+
+
+def _numbers(cmd):
+    r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr[-500:])
-    beside, least, full = (int(x) for x in r.stdout.split())
-    print(beside, least, full)
+    print(r.stdout)
+    return (int(x) for x in r.stdout.split())
+
+
+def test_gradient_runs_in_less_memory_than_its_largest_batch(tmp_path):
+    beside, least, full = _numbers([_program(tmp_path)])
     # the classes one by one, and rows by the piece, take less than half of what the batch takes
     assert least - beside < 0.5 * (full - beside)
+
+
+def test_product_runs_without_room_for_its_partial_tiles(tmp_path):
+    prepared, least, full = _numbers([_program(tmp_path), "sigma"])
+    # the tables of a product's units and items remain
+    assert least - prepared < 0.5 * (full - prepared)
