@@ -299,7 +299,7 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
     hip_check(hipMemcpyAsync(t.tables.p, gp.packed.data(), gp.packed.size(), hipMemcpyHostToDevice, st), "grad tables");
     launch_grad_expand(gp.view(t.tables.as<char>()), left, (left ? envl : envr).buf.as<double>(), A.buf.as<double>(),
                        out, t.units.as<GemmUnit>(), t.items.as<GemmItem>(), st);
-    launch_gemm_w32(GEMM_NN, 0, gp.buf, t.units.as<GemmUnit>(), (int)gp.units, t.items.as<GemmItem>(), st);
+    launch_gemm_w32(GEMM_NN, gp.buf, t.units.as<GemmUnit>(), (int)gp.units, t.items.as<GemmItem>(), st);
   };
   auto flush = [&]() {
     if (batch.empty()) return;

@@ -191,9 +191,9 @@ __global__ __launch_bounds__(256) void gemm_f32(const GemmUnit* __restrict__ uni
       }
 }
 
-// bf16 operands, fp32 accumulation: A given as TA (bf16 bits or fp32, rounded to
-// bf16 in LDS), B as bf16 bits.  One v_mfma_f32_16x16x16_bf16 per 16-deep k tile.
-template <int MODE, typename TA>
+// bf16 operands, fp32 accumulation (A times the item's coefficient is rounded to bf16
+// in LDS).  One v_mfma_f32_16x16x16_bf16 per 16-deep k tile.
+template <int MODE>
 __global__ __launch_bounds__(256) void gemm_bf16(const GemmUnit* __restrict__ units,
                                                  const GemmItem* __restrict__ items) {
   __shared__ uint16_t As[TK][LDP];
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(256) void gemm_bf16(const GemmUnit* __restrict__ un
     for (int j = 0; j < 2; ++j) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
   for (int it = u.ib; it < u.ie; ++it) {
     const GemmItem g = items[it];
-    const TA* A = (const TA*)g.A;
+    const uint16_t* A = (const uint16_t*)g.A;
     const uint16_t* B = (const uint16_t*)g.B;
     const float coef = (float)g.coef;
     for (int k0 = 0; k0 < g.K; k0 += TK) {
@@ -537,9 +537,7 @@ __device__ inline void w32_tile(const GemmUnit& u, const GemmItem* __restrict__ 
       }
 }
 
-// TAG only names otherwise identical instantiations, so a profiler can tell
-// launches apart (e.g. sigma phases, timed and untimed work).
-template <int MODE, int TAG, bool BUF>
+template <int MODE, bool BUF>
 __global__ __launch_bounds__(256) void gemm_f64_w32(const GemmUnit* __restrict__ units,
                                                     const GemmItem* __restrict__ items, int n_units) {
   // the wave index is uniform across the wave; saying so keeps the unit and item
@@ -1056,27 +1054,14 @@ inline int grid_for(long n, int bs = 256, int cap = 4096) {
 
 }  // namespace
 
-void launch_gemm_w32(int mode, int tag, bool buf, const GemmUnit* units, int n_units, const GemmItem* items,
-                     hipStream_t s) {
+void launch_gemm_w32(int mode, bool buf, const GemmUnit* units, int n_units, const GemmItem* items, hipStream_t s) {
   if (n_units <= 0) return;
   dim3 grid((n_units + 3) / 4), block(256);
-  if (!buf || mode == GEMM_TN) {
-    if (mode == GEMM_NN) gemm_f64_w32<GEMM_NN, 0, false><<<grid, block, 0, s>>>(units, items, n_units);
-    else if (mode == GEMM_NT) gemm_f64_w32<GEMM_NT, 0, false><<<grid, block, 0, s>>>(units, items, n_units);
-    else gemm_f64_w32<GEMM_TN, 0, false><<<grid, block, 0, s>>>(units, items, n_units);
-    return;
-  }
-#define DMRG_W32_LAUNCH(T)                                                                            \
-  if (mode == GEMM_NN) gemm_f64_w32<GEMM_NN, T, true><<<grid, block, 0, s>>>(units, items, n_units); \
-  else gemm_f64_w32<GEMM_NT, T, true><<<grid, block, 0, s>>>(units, items, n_units);
-  switch (tag) {
-    case 1: DMRG_W32_LAUNCH(1) break;
-    case 2: DMRG_W32_LAUNCH(2) break;
-    case 3: DMRG_W32_LAUNCH(3) break;
-    case 4: DMRG_W32_LAUNCH(4) break;
-    default: DMRG_W32_LAUNCH(0) break;
-  }
-#undef DMRG_W32_LAUNCH
+  if (mode == GEMM_TN) gemm_f64_w32<GEMM_TN, false><<<grid, block, 0, s>>>(units, items, n_units);
+  else if (mode == GEMM_NN && buf) gemm_f64_w32<GEMM_NN, true><<<grid, block, 0, s>>>(units, items, n_units);
+  else if (mode == GEMM_NN) gemm_f64_w32<GEMM_NN, false><<<grid, block, 0, s>>>(units, items, n_units);
+  else if (buf) gemm_f64_w32<GEMM_NT, true><<<grid, block, 0, s>>>(units, items, n_units);
+  else gemm_f64_w32<GEMM_NT, false><<<grid, block, 0, s>>>(units, items, n_units);
 }
 
 void launch_grad_expand(const GradView& v, bool left, const double* env, const double* site, double* out,
@@ -1108,12 +1093,9 @@ void launch_gemm(int prec, int mode, const GemmUnit* units, int n_units, const G
     if (mode == GEMM_NN) gemm_f32<GEMM_NN, float, float><<<grid, block, 0, s>>>(units, items);
     else if (mode == GEMM_NT) gemm_f32<GEMM_NT, float, float><<<grid, block, 0, s>>>(units, items);
     else gemm_f32<GEMM_TN, float, float><<<grid, block, 0, s>>>(units, items);
-  } else if (prec == PREC_BF16) {  // A: bf16, B: bf16
-    if (mode == GEMM_NN) gemm_bf16<GEMM_NN, uint16_t><<<grid, block, 0, s>>>(units, items);
-    else gemm_bf16<GEMM_NT, uint16_t><<<grid, block, 0, s>>>(units, items);
-  } else {  // A: fp32 rounded to bf16 on load, B: bf16
-    if (mode == GEMM_NN) gemm_bf16<GEMM_NN, float><<<grid, block, 0, s>>>(units, items);
-    else gemm_bf16<GEMM_NT, float><<<grid, block, 0, s>>>(units, items);
+  } else {  // PREC_BF16; no TN
+    if (mode == GEMM_NN) gemm_bf16<GEMM_NN><<<grid, block, 0, s>>>(units, items);
+    else gemm_bf16<GEMM_NT><<<grid, block, 0, s>>>(units, items);
   }
 }
 

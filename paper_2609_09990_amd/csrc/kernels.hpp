@@ -50,8 +50,7 @@ void launch_gemm(int prec, int mode, const GemmUnit* units, int n_units, const G
 // the full tile, row-major (tile rows x tile cols), to a partial slot (split-K).
 // buf: NN / NT launch whose items all pass buffer_reach_ok (raw buffer loads);
 // otherwise plain loads (and any mode).
-void launch_gemm_w32(int mode, int tag, bool buf, const GemmUnit* units, int n_units, const GemmItem* items,
-                     hipStream_t s);
+void launch_gemm_w32(int mode, bool buf, const GemmUnit* units, int n_units, const GemmItem* items, hipStream_t s);
 // Whether one item may take the buffer-load path: every element offset a tile
 // forms from the operand starts (up to 32 past the last row's K, NN rows of B up
 // to K + 32) stays below 1 GiB in bytes, so offsets fit 32-bit arithmetic.

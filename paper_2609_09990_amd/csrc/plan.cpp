@@ -715,7 +715,7 @@ void Solver::launch_resolved(Phase& ph, int prec, int slot) {
   const GemmUnit* units = ph.d_units[slot].as<GemmUnit>();
   const GemmItem* items = ph.d_items[slot].as<GemmItem>();
   if (ph.stream) launch_gemm_stream(prec, prec == PREC_F64 ? ph.tag : 0, units, ph.n_units[slot], items, st);
-  else launch_gemm_w32(ph.mode, ph.tag, ph.buf_ok[slot], units, ph.n_units[slot], items, st);
+  else launch_gemm_w32(ph.mode, ph.buf_ok[slot], units, ph.n_units[slot], items, st);
   if (prec == PREC_F64) {
     if (ph.gemm_done) (void)hipEventRecord(ph.gemm_done, st);  // GEMM-only timing
     launch_splitk_reduce(ph.d_tiles[slot].as<SplitTile>(), ph.n_tiles[slot], splitk_.as<double>(), st);
@@ -1367,14 +1367,13 @@ void Solver::build_sigma_plan(int k) {
               (int)item_at[i], (int)(item_at[i] + merged[i].items.size()), br.c == 0 ? 0 : 1);
   }
   merged.clear();
-  // split-K granularity of every chunk from the work of all chunks of the phase
+  // split-K granularity of every chunk from the work of all chunks of phase B
   // (pieces of the same size whatever the chunking)
-  for (std::vector<Phase>* v : {&phA_, &phB_}) {
-    if (v->size() <= 1) continue;
+  if (nch > 1) {
     double w[2] = {0, 0};
-    for (const Phase& ph : *v)
+    for (const Phase& ph : phB_)
       for (int c = 0; c < 2; ++c) w[c] += phase_work(ph, c != 0);
-    for (Phase& ph : *v)
+    for (Phase& ph : phB_)
       for (int c = 0; c < 2; ++c) ph.split_work[c] = w[c];
   }
   if (opt_.verbose > 1) {
@@ -1382,7 +1381,8 @@ void Solver::build_sigma_plan(int k) {
     fprintf(stderr, "sigma plan k=%d (%d threads): items %.2f ms (generation %.2f), phase A %.2f ms, phase B %.2f ms\n",
             k, plan_threads(), ms(tp0, tp1), ms(tp0, tp05), ms(tp1, tp2), ms(tp2, clk::now()));
     // shape statistics: executed (tile-padded) vs useful flops per phase
-    for (const Phase* ph : {&phB_[0]}) {
+    {
+      const Phase* ph = &phB_[0];
       double padded = 0, kpad = 0, ksum = 0;
       long nit = 0;
       for (const PUnit& u : ph->units)
@@ -1393,8 +1393,8 @@ void Solver::build_sigma_plan(int k) {
           ksum += K;
           ++nit;
         }
-      fprintf(stderr, "plan k=%d phase %s: units %zu items %zu (unit-items %ld) useful %.3e padded %.3e (x%.1f) "
-              "mean K %.1f (padded %.1f)\n", k, "B", ph->units.size(), ph->items.size(), nit,
+      fprintf(stderr, "plan k=%d phase B: units %zu items %zu (unit-items %ld) useful %.3e padded %.3e (x%.1f) "
+              "mean K %.1f (padded %.1f)\n", k, ph->units.size(), ph->items.size(), nit,
               ph->flops, padded, padded / std::max(ph->flops, 1.0), ksum / std::max(nit, 1L), kpad / std::max(nit, 1L));
     }
     {
