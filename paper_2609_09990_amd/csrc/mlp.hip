@@ -79,16 +79,18 @@ __global__ void layer1_kernel(const float* __restrict__ X, long n, int nin, cons
 }
 
 // One wave per row.
-__global__ void layer3_kernel(const float* __restrict__ z2, long n, int width, const float* __restrict__ b2,
-                              const float* __restrict__ W3, const float* __restrict__ b3, float* __restrict__ y) {
+__global__ void layer3_kernel(float* __restrict__ z2, long n, int width, const float* __restrict__ b2,
+                              const float* __restrict__ W3, const float* __restrict__ b3, float* __restrict__ y,
+                              int store) {
   const int lane = threadIdx.x & 63;
   const long row = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (row >= n) return;
-  const float* zr = z2 + row * width;
+  float* zr = z2 + row * width;
   double acc = 0.0;
   for (int j = lane; j < width; j += 64) {
     float a = fmaxf(zr[j] + b2[j], 0.f);
     acc += (double)a * W3[j];
+    if (store) zr[j] = a;
   }
   acc = wave_sum(acc);
   if (lane == 0) y[row] = (float)(acc + b3[0]);
@@ -729,16 +731,19 @@ __global__ void triple_target_kernel(const double* __restrict__ psi_i, const dou
 void launch_mlp_layer1(const float* X, long n, int nin, const float* W1, const float* b1, int width, float* a1,
                        uint16_t* a1b, hipStream_t s) {
   if (n <= 0) return;
-  if (a1 && !a1b && width % 4 == 0 && kThreads % (width / 4) == 0 && nin <= kL1MaxIn) {
+  // a thread's weights take longer to load than few rows to form: from 2^18 activations
+  // on (width 256: 1 row 37 us per forward against 41, 1332 rows 48.3 against 47.7, 3000 rows
+  // 57 against 50; width 128: 1332 rows 33 against 35, 6000 rows 44 against 38)
+  if (a1 && !a1b && width % 4 == 0 && kThreads % (width / 4) == 0 && nin <= kL1MaxIn && n * width >= (1L << 18)) {
     const long rows = kThreads / (width / 4);
     layer1_cols_kernel<<<(int)std::min<long>((n + 4 * rows - 1) / (4 * rows), 2048), kThreads, 0, s>>>(X, n, nin, W1, b1, width, a1);
     return;
   }
   layer1_kernel<<<grid_of(n * width), kThreads, 0, s>>>(X, n, nin, W1, b1, width, a1, a1b);
 }
-void launch_mlp_layer3(const float* z2, long n, int width, const float* b2, const float* W3, const float* b3, float* y,
-                       hipStream_t s) {
-  if (n > 0) layer3_kernel<<<(int)((n + 3) / 4), kThreads, 0, s>>>(z2, n, width, b2, W3, b3, y);
+void launch_mlp_layer3(float* z2, long n, int width, const float* b2, const float* W3, const float* b3, float* y,
+                       bool store, hipStream_t s) {
+  if (n > 0) layer3_kernel<<<(int)((n + 3) / 4), kThreads, 0, s>>>(z2, n, width, b2, W3, b3, y, store ? 1 : 0);
 }
 bool launch_mlp_infer_bf16(const float* X, long n, int nin, const float* W1, const float* b1, int width,
                            const uint16_t* W2b, const float* b2, const float* W3, const float* b3, float* y,
@@ -759,6 +764,15 @@ void launch_cos_grad(const float* y, const float* t, const double* stats, int ns
                      hipStream_t s) {
   long n = (long)nseg * seglen;
   if (n > 0) cos_grad_kernel<<<grid_of(n), kThreads, 0, s>>>(y, t, stats, nseg, seglen, dy);
+}
+// Few 128-row tiles leave most of the chip idle and the tile's chain of MFMAs and
+// its row sums in the open: below 64 of them the plain 64 x 64 tiles and a wave per
+// row are faster (width 256: 1 row 37 us per call against 43, 1332 rows 48 against 54,
+// 3000 rows, 48 tiles, 50 against 55; 6000 rows, 94 tiles, 72 against 61; width 512: 1332
+// rows, 44 tiles, 74 against 81, 3000 rows, 96 tiles, 108 against 85).
+bool mlp_few_tiles(long n, int width) {
+  const int tn = width <= 64 ? 64 : 128;
+  return ((n + kMT - 1) / kMT) * ((width + tn - 1) / tn) < 64;
 }
 int mlp_layer3_parts(int width) { return width <= 64 ? 1 : (width + 127) / 128 * 2; }
 int mlp_row_tiles(long n) { return (int)((n + kMT - 1) / kMT); }

@@ -23,12 +23,13 @@ bool launch_mlp_infer_bf16(const float* X, long n, int nin, const float* W1, con
                            hipStream_t s);
 void launch_mlp_layer1(const float* X, long n, int nin, const float* W1, const float* b1, int width,
                        float* a1, uint16_t* a1b, hipStream_t s);
-// y[i] = b3 + sum_j max(0, z2[i][j] + b2[j]) W3[j].
-void launch_mlp_layer3(const float* z2, long n, int width, const float* b2, const float* W3, const float* b3,
-                       float* y, hipStream_t s);
+// y[i] = b3 + sum_j max(0, z2[i][j] + b2[j]) W3[j]; if store, z2 <- max(0, z2 + b2).
+void launch_mlp_layer3(float* z2, long n, int width, const float* b2, const float* W3, const float* b3, float* y,
+                       bool store, hipStream_t s);
 // fp32 hidden and output layer: a2 = relu(a1 W2^T + b2) (stored unless null),
 // y = a2 W3^T + b3; part: mlp_layer3_parts(width) x n doubles of scratch.
 int mlp_layer3_parts(int width);
+bool mlp_few_tiles(long n, int width);
 void launch_mlp_forward_f32(const float* a1, long n, int width, const float* W2, const float* b2, const float* W3,
                             const float* b3, float* a2, double* part, float* y, hipStream_t s);
 // Their backward from dy: gradients of W1, b1, W2, b2, W3 (overwritten).  Scratch:
@@ -90,7 +91,9 @@ class MLP {
   DevMem p_, m_, v_, grad_, w2b_;
   DevMem a1_, a1b_, z2_, y_, dy_, stats_, part_, gpart_;
   int t_ = 0;
-  // cached GEMM tables of the hidden layer (bf16 inference of other widths)
+  // fp32 layers 1 to 3 into y; keep: the activations stay in a1_ and z2_
+  void forward_f32(const float* X, long n, float* y, bool keep, hipStream_t s);
+  // cached GEMM tables of the hidden layer (fp32 of few rows; bf16 inference of other widths)
   struct Tables {
     const void* key[3] = {nullptr, nullptr, nullptr};
     long rows = -1;
@@ -98,8 +101,8 @@ class MLP {
     std::vector<GemmUnit> hu;
     std::vector<GemmItem> hi;
     int nu = 0;
-  } ti_;
-  void gemm(Tables& t, const void* A, const void* B, void* C, long rows, hipStream_t s);
+  } tz_, ti_;
+  void gemm(Tables& t, int prec, const void* A, const void* B, void* C, long rows, hipStream_t s);
   void refresh_bf16();
 };
 

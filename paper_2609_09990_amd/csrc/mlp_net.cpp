@@ -64,9 +64,9 @@ void MLP::get_params(float* host) const {
   hip_check(hipStreamSynchronize(st_), "mlp params");
 }
 
-// C[rows x W] = A[rows x W] W2^T (bf16 operands) on 64 x 64 tiles: one item per
-// 64-row tile (the A operand moves with the tile), all W columns.
-void MLP::gemm(Tables& t, const void* A, const void* B, void* C, long rows, hipStream_t s) {
+// C[rows x W] = A[rows x W] W2^T (operands of `prec`) on 64 x 64 tiles: one item
+// per 64-row tile (the A operand moves with the tile), all W columns.
+void MLP::gemm(Tables& t, int prec, const void* A, const void* B, void* C, long rows, hipStream_t s) {
   if (t.key[0] != A || t.key[1] != B || t.key[2] != C || t.rows != rows) {
     hip_check(hipStreamSynchronize(s), "mlp tables");  // earlier uploads of the staging vectors are done
     t.rows = -1;  // no tables until these are uploaded
@@ -74,7 +74,7 @@ void MLP::gemm(Tables& t, const void* A, const void* B, void* C, long rows, hipS
     t.hi.clear();
     for (long m0 = 0; m0 < rows; m0 += 64) {
       int ib = (int)t.hi.size();
-      t.hi.push_back({(const char*)A + m0 * w_ * 2, B, w_, w_, w_, 0, 1.0});
+      t.hi.push_back({(const char*)A + m0 * w_ * (prec == PREC_BF16 ? 2 : 4), B, w_, w_, w_, 0, 1.0});
       char* Cm = (char*)C + m0 * w_ * 4;
       const int M = (int)std::min<long>(64, rows - m0);
       for (int n0 = 0; n0 < w_; n0 += 64) t.hu.push_back({Cm, w_, M, w_, 0, n0, ib, ib + 1, 0});
@@ -89,7 +89,7 @@ void MLP::gemm(Tables& t, const void* A, const void* B, void* C, long rows, hipS
     t.rows = rows;
     t.nu = (int)t.hu.size();
   }
-  launch_gemm(PREC_BF16, GEMM_NT, t.du.as<GemmUnit>(), t.nu, t.di.as<GemmItem>(), s);
+  launch_gemm(prec, GEMM_NT, t.du.as<GemmUnit>(), t.nu, t.di.as<GemmItem>(), s);
 }
 
 void MLP::forward(int prec, const float* X, long n, float* y, hipStream_t s) {
@@ -104,15 +104,27 @@ void MLP::forward(int prec, const float* X, long n, float* y, hipStream_t s) {
     z2_.reserve((size_t)n * w_ * 4);
     a1b_.reserve((size_t)n * w_ * 2);
     launch_mlp_layer1(X, n, nin_, P + oW1_, P + ob1_, w_, nullptr, a1b_.as<uint16_t>(), s);
-    gemm(ti_, a1b_.p, w2b_.p, z2_.p, n, s);
-    launch_mlp_layer3(z2_.as<float>(), n, w_, P + ob2_, P + oW3_, P + ob3_, y, s);
+    gemm(ti_, PREC_BF16, a1b_.p, w2b_.p, z2_.p, n, s);
+    launch_mlp_layer3(z2_.as<float>(), n, w_, P + ob2_, P + oW3_, P + ob3_, y, false, s);
     return;
   }
+  forward_f32(X, n, y, false, s);
+}
+
+void MLP::forward_f32(const float* X, long n, float* y, bool keep, hipStream_t s) {
+  const float* P = p_.as<float>();
+  const bool few = mlp_few_tiles(n, w_);
   a1_.reserve((size_t)n * w_ * 4);
-  part_.reserve((size_t)mlp_layer3_parts(w_) * n * 8);
+  if (few || keep) z2_.reserve((size_t)n * w_ * 4);
+  if (!few) part_.reserve((size_t)mlp_layer3_parts(w_) * n * 8);
   launch_mlp_layer1(X, n, nin_, P + oW1_, P + ob1_, w_, a1_.as<float>(), nullptr, s);
-  launch_mlp_forward_f32(a1_.as<float>(), n, w_, P + oW2_, P + ob2_, P + oW3_, P + ob3_, nullptr, part_.as<double>(),
-                         y, s);
+  if (few) {
+    gemm(tz_, PREC_F32, a1_.p, P + oW2_, z2_.p, n, s);
+    launch_mlp_layer3(z2_.as<float>(), n, w_, P + ob2_, P + oW3_, P + ob3_, y, keep, s);
+  } else {
+    launch_mlp_forward_f32(a1_.as<float>(), n, w_, P + oW2_, P + ob2_, P + oW3_, P + ob3_,
+                           keep ? z2_.as<float>() : nullptr, part_.as<double>(), y, s);
+  }
 }
 
 double MLP::loss_grad(const float* X, const float* T, int nseg, int seglen) {
@@ -120,8 +132,6 @@ double MLP::loss_grad(const float* X, const float* T, int nseg, int seglen) {
   const long n = (long)nseg * seglen;
   const float* P = p_.as<float>();
   float* G = grad_.as<float>();
-  a1_.reserve((size_t)n * w_ * 4);
-  z2_.reserve((size_t)n * w_ * 4);
   y_.reserve((size_t)n * 4);
   dy_.reserve((size_t)n * 4);
   stats_.reserve((size_t)nseg * 3 * 8);
@@ -129,9 +139,7 @@ double MLP::loss_grad(const float* X, const float* T, int nseg, int seglen) {
   part_.reserve((size_t)std::max((long)mlp_layer3_parts(w_) * n, std::max(2 * nch, (nin_ + 1) * nrt) * w_) * 8);
   gpart_.reserve((size_t)nch * w_ * w_ * 4);
   // forward (fp32), keeping a1 and a2 (z2_ holds a2)
-  launch_mlp_layer1(X, n, nin_, P + oW1_, P + ob1_, w_, a1_.as<float>(), nullptr, st_);
-  launch_mlp_forward_f32(a1_.as<float>(), n, w_, P + oW2_, P + ob2_, P + oW3_, P + ob3_, z2_.as<float>(),
-                         part_.as<double>(), y_.as<float>(), st_);
+  forward_f32(X, n, y_.as<float>(), true, st_);
   // loss and dL/dy
   launch_seg_stats(y_.as<float>(), T, nseg, seglen, stats_.as<double>(), st_);
   launch_cos_grad(y_.as<float>(), T, stats_.as<double>(), nseg, seglen, dy_.as<float>(), st_);
