@@ -257,6 +257,11 @@ __global__ __launch_bounds__(kThreads, 2) void uv_kernel(const double* __restric
 #pragma unroll
       for (int q = 0; q < 4; ++q) w[q] += w2[q];
       if (q0 > 0) __syncthreads();  // Wq of the previous pass is read
+      // rows past the last factor are zeros, also where T is not finite (0 x inf)
+      if (q0 + kUQ > nq) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q] = q0 + 16 * (wave >> 1) + kq + 4 * q < nq ? w[q] : 0.0;
+      }
 #pragma unroll
       for (int q = 0; q < 4; ++q) Wq[(16 * (wave >> 1) + kq + 4 * q) * kUPitch + 16 * (wave & 1) + r] = w[q];
       __syncthreads();

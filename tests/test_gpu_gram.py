@@ -119,3 +119,15 @@ def test_apply_v_many_slices(n, na, nb, nq):
     U = np.tensordot(F.T @ F, T, axes=1)
     ref = 0.5 * sum(space.apply_E(x // n, x % n, U[x]) for x in range(n * n))
     assert np.abs(got - ref).max() <= 1e-12 * max(np.abs(ref).max(), 1.0)
+
+
+# an infinite amplitude gives infinities where every term has one sign: the rows that fill a block of
+# factors or determinants up bring no 0 x inf into it
+@pytest.mark.parametrize("nq", [1, 3, 4, 66])
+def test_apply_v_of_an_infinite_amplitude(nq):
+    torch, prob, _, space, rng = _setup(3, 1, 0, nq)
+    import paper_2609_09990_amd as pk
+    B = rng.uniform(0.5, 1.0, (nq, 3, 3))
+    prob = pk.Problem(np.eye(3), B + B.transpose(0, 2, 1), 1, 0, 0.0)
+    c = torch.tensor([1.0, np.inf, 2.0], dtype=torch.float64, device="cuda")
+    assert torch.isposinf(prob.ci_apply_v(c)).all()
