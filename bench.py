@@ -26,10 +26,11 @@ METRIC = "sigma TFLOP/s + sweep s, CAS(20,20) M=1024; learned vs plain time to 1
 N_ORB, N_CHOL, M, SEED = 20, 120, 1024, 0
 MID = N_ORB // 2 - 1
 PEAK_FP64 = 78.6  # TFLOP/s, MI355X dense FP64 matrix
-# HBM bytes per launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
-# runs, scaled by the same counters on a plain copy (fetch x2.0, write x1.0); None where the
-# kernel has changed since they were taken.
-TRAFFIC = None
+# Bytes beyond L2 per launch of the dominant kernel at this workload, from rocprofv3 --pmc FETCH_SIZE
+# / WRITE_SIZE runs (the step kernels under profiles/), scaled by the same counters on a plain
+# copy (fetch x2.0, write x1.0); most reads are served by the last-level cache.  Set to None whenever
+# that kernel changes.
+TRAFFIC = 3.95e10
 
 
 def _host_info():
@@ -434,7 +435,7 @@ def next_rows(pk, torch):
     g, G, ov = prob.ci_rdm12(c)
     t_12 = time.time() - t0
     rows = 12 * 12 + 1
-    f12 = 2.0 * rows * rows * na * nb
+    f12 = 1.0 * rows * (rows + 1) * na * nb  # bra is ket: half of the products
     t0 = time.time()
     vc = prob.ci_apply_v(c)
     torch.cuda.synchronize()
@@ -442,7 +443,7 @@ def next_rows(pk, torch):
     t0 = time.time()
     F = prob.ci_rdm3(c, vc)
     t_3 = time.time() - t0
-    f3 = 2.0 * rows * (144 * rows) * na * nb
+    f3 = 2.0 * 144 * (144 * 145 // 2 + 144) * na * nb  # E_rs E_tu for rs >= tu, and E_rs alone
     t0 = time.time()
     s1, I = prob.mutual_information(c)
     order, _ = pk.fiedler_order(I)

@@ -327,10 +327,10 @@ dmrg_status dmrg_mps_to_ci(dmrg_solver* s, int state, double* c, int64_t n);
  *   Gamma[((p*n+q)*n+r)*n+s] = <bra|E_pq E_rs|ket> - d_qr gamma_ps
  *     = sum_{sigma tau} <bra|a+_{p sigma} a+_{r tau} a_{s tau} a_{q sigma}|ket>,
  * overlap = <bra|ket>; host outputs (n^2, n^4 doubles, 1; each may be NULL).
- * At most 16 orbitals.  E_rs c for all rs in passes of determinants (a gather
- * kernel over string-excitation tables), then one fp64 MFMA product of
- * (n^2 + 1) x (n^2 + 1) over the determinants; runs on `stream` and returns
- * when the outputs are written. */
+ * At most 16 orbitals.  One fp64 MFMA product of (n^2 + 1) x (n^2 + 1) over the
+ * determinants, the excited vectors E_rs c gathered through string-excitation
+ * tables where it uses them; runs on `stream` and returns when the outputs are
+ * written. */
 dmrg_status dmrg_ci_rdm12(const dmrg_problem* p, int64_t n, const double* bra, const double* ket, double* gamma, double* Gamma,
                           double* overlap, void* stream);
 /* The all-active two-electron operator on a device CI vector (the fused
@@ -338,15 +338,17 @@ dmrg_status dmrg_ci_rdm12(const dmrg_problem* p, int64_t n, const double* bra, c
  * into the ket, so <EEEE>-type densities contracted with it are three-body
  * densities of (bra, V ket) and the n^8 object is never formed):
  *   out = V c,  V = 1/2 sum_pqrs (pq|rs) E_pq E_rs,  (pq|rs) = sum_Q B^Q_pq B^Q_rs,
- * streamed through the problem's Cholesky factors (E_rs c for all rs, two
- * GEMMs over the factors, one gather sum); out: device, same length as c, not
- * aliasing it.  At most 16 orbitals. */
+ * streamed through the problem's Cholesky factors B (U = B^T (B T) for the rows
+ * T_rs = E_rs c, formed in one kernel 32 determinants at a time, then a gather
+ * sum of E_pq U_pq; U, n_orb^2 vectors, is the scratch); out: device, same length
+ * as c, not aliasing it.  At most 16 orbitals. */
 dmrg_status dmrg_ci_apply_v(const dmrg_problem* p, int64_t n, const double* c, double* out, void* stream);
 /* Transition three-body density of device CI vectors (unnormalised):
  *   Gamma3[((((p*n+q)*n+r)*n+s)*n+t)*n+u] = <bra|E_pq E_rs E_tu|ket>
- * (host, n^6 doubles).  E_tu ket is kept for all tu, E_rs of each is formed in
- * passes of determinants and the fp64 MFMA split-K product with the bra's
- * copies accumulates the density.  At most 12 orbitals.  With ket = V c
+ * (host, n^6 doubles).  E_qp bra and E_tu ket are kept for all pairs (n_orb^2
+ * vectors each), E_rs of the latter is formed inside one fp64 MFMA product over
+ * the determinants, for rs >= tu; the other half follows from the commutator of
+ * E_rs and E_tu.  At most 12 orbitals.  With ket = V c
  * (dmrg_ci_apply_v) it gives sum_vwxy (vw|xy)/2 <bra|E_pq E_rs E_tu E_vw E_xy|c>. */
 dmrg_status dmrg_ci_rdm3(const dmrg_problem* p, int64_t n, const double* bra, const double* ket, double* Gamma3,
                          void* stream);

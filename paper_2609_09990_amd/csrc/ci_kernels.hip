@@ -1,8 +1,9 @@
 // Determinant-space kernels (device CI pipeline, Sec. III): the scatter of an
 // MPS's prefix x suffix amplitudes into the CI matrix, the excited copies
-// E_rs c of a CI vector, and the assembly of the one- and two-body (transition)
-// density matrices from their products.  All three are bandwidth-bound element
-// loops; the contraction between them runs on the fp64 MFMA block kernel.
+// E_rs c of a CI vector (three-body density), the sum of E_pq U_pq (V c), and the
+// assembly of the one-, two- and three-body (transition) density matrices.  All
+// are bandwidth-bound element loops; the contractions between them are in
+// ci_gram.hip.
 #include "ci.hpp"
 
 namespace dmrg {

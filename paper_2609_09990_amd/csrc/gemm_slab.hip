@@ -24,8 +24,8 @@
 //    kq holds 2 kq and 2 kq + 1), at most four left over as one step; bf16 sixteen
 //    at a time: fp32 and bf16 results keep their bits.
 //
-// Phase A at CAS(20,20), M = 1024: 2.8 -> 1.69 ms, of which writing the 4.5 GB of T
-// takes 0.75 and the MFMAs 0.75; CAS(12,12), M = 512: 420 -> 272 us; CAS(16,16),
+// Phase A at CAS(20,20), M = 1024: 2.8 -> 1.69 ms (random state; 2.87 -> 1.83 on that of
+// a half sweep), of which writing the 4.5 GB of T takes 0.75 and the MFMAs 0.75; CAS(12,12), M = 512: 420 -> 272 us; CAS(16,16),
 // M = 512, fp32: 388 -> 164 us, bf16: 376 -> 135 us.  (Storing a tile behind the next
 // one's first loads, so that no load waits for stores, spills: 1.94 ms.)
 #include <hip/hip_runtime.h>

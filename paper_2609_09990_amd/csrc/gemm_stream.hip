@@ -25,13 +25,14 @@
 //    item's K are read (DevMem keeps 64 readable bytes past every buffer) and
 //    replaced by zeros in both operands.
 //
-// This phase at CAS(20,20), M = 1024: 7.5 -> 5.3 ms (37 GB of L2 misses; without the
-// MFMAs 4.8 ms, with A from one place 2.8); CAS(12,12), M = 512: 1.36 -> 1.07 ms;
-// CAS(16,16), M = 512, with the bits of the kernels before: fp32 1.34 -> 0.84 ms,
-// bf16 0.94 -> 0.76 ms.  64-byte-wide windows (SL = 4) took 6.3 ms in fp64.
+// This kernel on a random state (mean K 12) of CAS(20,20), M = 1024, against the
+// workgroup kernel of up to 96 x 64 before it: 7.5 -> 5.20 ms (37 GB of L2 misses;
+// without the MFMAs 4.8 ms, with A from one place 2.8); on the state of a half sweep
+// there (mean K 23, blocks of up to 82 x 62) 5.46 -> 5.37 ms (39 GB, where that kernel,
+// whose waves shared A, missed 25).  CAS(12,12), M = 512: 1.36 -> 1.07 ms; CAS(16,16),
+// M = 512, with the bits of the kernels before: fp32 1.34 -> 0.82 ms, bf16 0.94 -> 0.75
+// ms.  64-byte-wide windows (SL = 4) took 6.3 ms in fp64.
 #include <hip/hip_runtime.h>
-
-#include <stdexcept>
 
 #include "bf16.hpp"
 #include "kernels.hpp"

@@ -4,13 +4,14 @@
 // new environment, or of an intermediate T = X psi) accumulates its block
 // products ("items") in a fixed order with MFMA, so results are bitwise
 // reproducible (no atomics; split-K partial tiles are summed in order by
-// splitk_reduce).  Long item lists (sigma phase B, fp64 / fp32) take the stream
-// kernel of gemm_stream.hip; here:
+// splitk_reduce).  Sigma takes the slab kernel (phase A, gemm_slab.hip) and the
+// stream kernel (phase B, gemm_stream.hip) in every precision, the gradient's
+// G = P Q^T the stream kernel; here:
 //  * w32_tile: one wave per (16 RB) x (16 CB) tile reading operands straight
-//    from memory (phase A, environment updates, gradient, fp32 / bf16 forms);
+//    from memory (fp64: environment updates, the gradient's row products);
 //  * gemm_f64 / gemm_f32 / gemm_bf16: plain 64 x 64 LDS tiles, four waves of
-//    32 x 32 (one-off products: two-site forms, overlaps, projections, the MLP,
-//    dmrg_block_gemm).
+//    32 x 32 (one-off products: two-site forms, overlaps, projections, the hidden
+//    layer of few rows, dmrg_block_gemm).
 // Plus the Davidson BLAS-1 kernels, the one-workgroup Jacobi eigensolver, the
 // diagonal, premix / pairmix and precision conversions.
 #include <hip/hip_runtime.h>
@@ -543,11 +544,10 @@ __global__ __launch_bounds__(256) void gemm_f64_w32(const GemmUnit* __restrict__
   // the wave index is uniform across the wave; saying so keeps the unit and item
   // descriptors (and the buffer resources built from them) in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  // NN launches (sigma phase A: a factor block feeds every column tile of its
+  // NN launches (a factor or environment block feeds every column tile of its
   // unit) give each XCD a contiguous range of units, so a block is fetched into
   // one XCD's L2; workgroups are dispatched to the 8 XCDs round-robin.  NT
-  // launches keep the plain order, which measured faster for sigma's long-K
-  // products when they ran on this kernel.
+  // launches keep the plain order.
   int wg = blockIdx.x;
   if constexpr (MODE == GEMM_NN) {
     const int nb = gridDim.x, q = nb >> 3, rem = nb & 7, x = wg & 7;

@@ -17,8 +17,8 @@ struct GemmItem {
 
 // One output tile (rows m0.., cols n0.., at most 64 x 64) of an M x N output
 // block; it accumulates items [ib, ie) in order (no atomics: deterministic).
-// shape (fp64 one-wave kernel only): 8 RB + CB for a (16 RB) x (16 CB) tile,
-// RB in 1..4, CB in 1..2 (0 = 32 x 32).
+// shape (one-wave and stream kernels): 8 RB + CB for a (16 RB) x (16 CB) tile, RB in
+// 1..4, CB in 1..2 (one-wave kernel, 0 = 32 x 32) or 1..4 (stream kernel).
 struct GemmUnit {
   void* C;
   int ldc, M, N, m0, n0, ib, ie, accumulate;

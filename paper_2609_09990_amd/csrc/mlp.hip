@@ -1,8 +1,9 @@
 // Learned Davidson preconditioner on gfx950: network kernels (forward, cosine
 // loss, backward, Adam), per-amplitude feature kernels and the gathering of
 // training triples.  Element-wise kernels and deterministic column reductions
-// (fixed chunks, partials summed in order); the hidden layer's GEMMs run on the
-// block-GEMM engine (see mlp_net.cpp).
+// (fixed chunks, partials summed in order); the hidden layer's products run on
+// mlp_gemm_kernel, those of few rows and of bf16 widths other than 256 on the
+// plain 64 x 64 tiles of kernels.hip (see mlp_net.cpp).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -474,10 +474,11 @@ void Solver::run_phase(Phase& ph, int prec, void* const* bases, size_t const* es
     }
   }, 4096);
   ph.buf_ok[slot] = buf_ok;
-  // NT phases with long item lists (sigma phase B) take the stream kernel: whole
-  // blocks up to 64 x 64 per wave, operands read once per block (phase B at
-  // CAS(20,20), M = 1024: 7.5 ms with 64-row workgroup tiles, one item at a time;
-  // 5.3 ms here); the others (fp64 only) the one-wave kernel
+  // NT phases with long item lists (sigma phase B, the gradient's G) take the
+  // stream kernel: whole blocks up to 64 x 64 per wave, operands read once per block
+  // (phase B at CAS(20,20), M = 1024, one item at a time on workgroup tiles against
+  // this: 7.5 and 5.2 ms on a random state, 5.46 and 5.37 on that of a half sweep);
+  // the others (fp64 only) the one-wave kernel
   const bool stream = ph.stream;
   DMRG_REQUIRE(stream || prec == PREC_F64, ST_EINVAL, "plan: no low-precision form of this phase");
   GemmUnit* units = nullptr;
