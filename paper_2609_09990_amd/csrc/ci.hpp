@@ -107,8 +107,9 @@ struct CiWork {
   DevMem T1, T2, part, G, out, lists, F;
   std::vector<DevMem*> scratch() { return {&T1, &T2, &part, &G, &out, &lists, &F}; }
 };
-class CiPool : public IdleMemory {
+class CiPool final : public IdleMemory {
  public:
+  CiPool() { enroll(); }
   ~CiPool() { retire(); }
   // holds the largest three-body density: (6, 6) electrons in 12 orbitals, two vectors,
   // 2.15e9 bytes (at 2 GiB every such call freed and allocated one set of copies)

@@ -118,7 +118,7 @@ IdleRegistry& idle_registry() {
 }
 }  // namespace
 
-IdleMemory::IdleMemory() {
+void IdleMemory::enroll() {
   IdleRegistry& r = idle_registry();
   std::lock_guard<std::mutex> l(r.m);
   r.all.insert(this);

@@ -124,9 +124,12 @@ class IdleMemory {
   virtual void drop() = 0;  // frees what no call is using; any thread
 
  protected:
-  IdleMemory();
+  IdleMemory() = default;
   virtual ~IdleMemory() = default;
-  void retire();  // no drop() after this; first in the destructor of every derived class
+  // drop() may come between the two: last in the constructor and first in the
+  // destructor of the class that implements it
+  void enroll();
+  void retire();
 };
 void drop_idle_memory();
 
@@ -319,8 +322,9 @@ struct MPSView {
 };
 
 // Buffers and tables of the integral gradient (grad.cpp), kept between calls.
-class GradWork : public IdleMemory {
+class GradWork final : public IdleMemory {
  public:
+  GradWork() { enroll(); }
   ~GradWork() { retire(); }
   struct Tables {
     DevMem tables, units, items;

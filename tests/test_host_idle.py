@@ -92,13 +92,93 @@ int main() {
 """
 
 
-def test_kept_memory_is_given_back_when_an_allocation_fails(tmp_path):
+THREADS = r"""
+#include <atomic>
+#include <cstdio>
+#include <thread>
+#include <vector>
+#include "ci.hpp"
+using namespace dmrg;
+extern "C" hipError_t hipMalloc(void** p, size_t n) {
+  if (n > 1000000) return hipErrorOutOfMemory;
+  *p = std::malloc(64);
+  return hipSuccess;
+}
+extern "C" hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
+extern "C" hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+static std::atomic<int> g_dropped{0};
+struct Early {  // runs while the object is under construction
+  Early() { drop_idle_memory(); }
+};
+struct Probe final : IdleMemory, Early {
+  Probe() { enroll(); }
+  ~Probe() { retire(); }
+  void drop() override { ++g_dropped; }
+};
+int main() {
+  {
+    Probe p;
+    if (g_dropped != 0) return 1;
+    drop_idle_memory();
+    if (g_dropped != 1) return 2;
+  }
+  drop_idle_memory();
+  if (g_dropped != 1) return 3;
+  std::atomic<bool> stop{false};
+  std::atomic<long> refused{0};
+  std::vector<std::thread> t;
+  for (int i = 0; i < 2; ++i)
+    t.emplace_back([&] {  // allocations that fail
+      while (!stop) {
+        DevMem d;
+        try {
+          d.reserve(2000000);
+        } catch (const Error&) {
+          ++refused;
+        }
+      }
+    });
+  for (int i = 0; i < 2; ++i)
+    t.emplace_back([&] {  // problems and gradients that come and go
+      for (int k = 0; k < 4000; ++k) {
+        CiPool pool;
+        auto w = pool.take();
+        w->T1.reserve(1000);
+        pool.give(std::move(w));
+        GradWork g;
+        GradWork::Use use(g);
+        g.P.reserve(1000);
+        if (!g.P.p) std::abort();
+      }
+    });
+  t[2].join();
+  t[3].join();
+  stop = true;
+  t[0].join();
+  t[1].join();
+  std::puts(refused > 0 ? "ok" : "idle");
+}
+"""
+
+
+def _run(tmp_path, source):
     import paper_2609_09990_amd as pk
     assert os.path.dirname(pk.LIB_PATH) == PKG
     src, exe = tmp_path / "idle.cpp", tmp_path / "idle"
-    src.write_text(SOURCE)
-    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(PKG, "csrc"),
-                    str(src), "-o", str(exe), "-L" + PKG, "-l:libdmrg_mi355x.so", "-Wl,-rpath," + PKG,
-                    "-Wl,-rpath,/opt/rocm/lib", "-Wl,--allow-shlib-undefined", "-rdynamic"], check=True)
-    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    src.write_text(source)
+    subprocess.run(["g++", "-std=c++17", "-pthread", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(PKG, "csrc"), str(src), "-o", str(exe), "-L" + PKG, "-l:libdmrg_mi355x.so",
+                    "-Wl,-rpath," + PKG, "-Wl,-rpath,/opt/rocm/lib", "-Wl,--allow-shlib-undefined", "-rdynamic"],
+                   check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", (r.returncode, r.stdout, r.stderr[-500:])
+
+
+def test_kept_memory_is_given_back_when_an_allocation_fails(tmp_path):
+    _run(tmp_path, SOURCE)
+
+
+def test_objects_that_come_and_go_while_allocations_fail(tmp_path):
+    """Nothing is dropped of an object that is being made or taken apart."""
+    _run(tmp_path, THREADS)
