@@ -325,10 +325,6 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
     grad_.Q.reserve(std::max<long>(bq, 1) * 8);
     grad_.G.reserve(std::max<long>(bg, 1) * 8);
     GradPlan pp, pq;
-    make_rows(true, pp);
-    run_rows(true, pp, grad_.tab[0], grad_.P.as<double>());
-    make_rows(false, pq);
-    run_rows(false, pq, grad_.tab[1], grad_.Q.as<double>());
     void* bases[B_NBUF] = {};
     bases[B_T] = grad_.P.p;
     bases[B_OUT] = grad_.Q.p;
@@ -338,7 +334,16 @@ void Solver::grad_site(int k, std::vector<double>& g, double* norm) {
     sizes[B_T] = bp;
     sizes[B_OUT] = bq;
     sizes[B_XMIX] = bg;
-    run_phase(pg, PREC_F64, bases, esz, sizes);
+    try {
+      make_rows(true, pp);
+      run_rows(true, pp, grad_.tab[0], grad_.P.as<double>());
+      make_rows(false, pq);
+      run_rows(false, pq, grad_.tab[1], grad_.Q.as<double>());
+      run_phase(pg, PREC_F64, bases, esz, sizes);
+    } catch (...) {
+      (void)hipStreamSynchronize(st);  // an upload may still read the packed tables
+      throw;
+    }
     Ghost.resize((size_t)bg);
     hip_check(hipMemcpyAsync(Ghost.data(), grad_.G.p, Ghost.size() * 8, hipMemcpyDeviceToHost, st), "grad G");
     hip_check(hipStreamSynchronize(st), "grad site");  // the packed tables and staging die here

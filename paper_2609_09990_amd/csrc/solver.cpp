@@ -472,8 +472,13 @@ void Solver::ensure_left(int c) {
   plan_k_ = -1;  // the update reuses the left premix buffer of the prepared step
   FactorSide fs;
   build_factor_side(fs, true, c - 1);
-  run_premix(fs, left_[c - 1]);
-  env_update_left(c - 1, fs);
+  try {
+    run_premix(fs, left_[c - 1]);
+    env_update_left(c - 1, fs);
+  } catch (...) {
+    (void)hipStreamSynchronize(st);  // an upload may still read fs, a kernel its tables
+    throw;
+  }
   hip_check(hipStreamSynchronize(st), "env left");
 }
 
@@ -495,8 +500,13 @@ void Solver::ensure_right(int c) {
   plan_k_ = -1;  // the update reuses the right premix buffer of the prepared step
   FactorSide fs;
   build_factor_side(fs, false, c);
-  run_premix(fs, right_[c + 1]);
-  env_update_right(c, fs);
+  try {
+    run_premix(fs, right_[c + 1]);
+    env_update_right(c, fs);
+  } catch (...) {
+    (void)hipStreamSynchronize(st);
+    throw;
+  }
   hip_check(hipStreamSynchronize(st), "env right");
 }
 
